@@ -185,7 +185,8 @@ int fmm_adjoint(fmm_plan *plan, const void *q_dev, const void *gbar_dev, const v
  *   far_weight    work of one surface source relative to a point source when
  *                 items are cut and ordered (1.15)
  *   gemm_rbw      16-row blocks per wave in the single-precision translation
- *                 GEMMs (0: automatic, 1 .. 8)
+ *                 GEMMs (0: automatic, 1 .. 8); the segmented M2L takes at
+ *                 most 3
  *   m2l_factored  1: each M2L operator (per level and offset, in the
  *                 truncated-SVD coordinates) is split by its own truncated
  *                 SVD, M ~ L R with rank k (singular values above 1e-7 of the
@@ -216,8 +217,9 @@ int fmm_adjoint(fmm_plan *plan, const void *q_dev, const void *gbar_dev, const v
  *                 one launch and the L2L levels in another (tasks in
  *                 dependency order, each level waiting on counters of the
  *                 one before, bounded waits); 0: one launch per level
- *   m2l_cols      bf16x3 M2L columns (V pairs) per workgroup sharing one
- *                 operator fetch: 64 (default) or 128
+ *   m2l_cols      bf16x3 M2L columns (one per target box and source parent)
+ *                 per workgroup sharing one operator fetch: 64 (default) or
+ *                 128
  *   gemm_narrow   pair evaluations in single precision: 1 runs the L2L and
  *                 the leaves' downward projections as one-wave workgroups
  *                 (room beside the near field's waves); 0: 256-thread ones

@@ -22,6 +22,8 @@
 
 namespace fmm {
 int eval_dispatch(fmm_plan *P, const void *q, int nrhs, void *pot, void *grad, hipStream_t s);
+int setup_products(const double *xyz_dev, int64_t n, int kernel, double kappa, int p, int ncrit, int precision,
+                   fmm_stream_t stream, fmm_plan **out);
 }
 
 using fmm::set_error;
@@ -1301,8 +1303,8 @@ int bem_setup(const double *verts, int64_t nv, const int32_t *tris, int64_t nt, 
     if (hipGetLastError() != hipSuccess) { set_error("bem_setup: launch failed"); rc = FMM_EHIP; break; }
     if ((rc = precond_setup(op, op->p1 ? FMM_BEM_PRECOND_MASS : FMM_BEM_PRECOND_BLOCK, s))) break;
     // the two FMM plans on the quadrature points
-    if ((rc = fmm_setup(op->d_qpts, op->N, FMM_LAPLACE, 0.0, p, ncrit, precision, stream, &op->fl))) break;
-    if ((rc = fmm_setup(op->d_qpts, op->N, FMM_YUKAWA, kappa, p, ncrit, precision, stream, &op->fy))) break;
+    if ((rc = fmm::setup_products(op->d_qpts, op->N, FMM_LAPLACE, 0.0, p, ncrit, precision, stream, &op->fl))) break;
+    if ((rc = fmm::setup_products(op->d_qpts, op->N, FMM_YUKAWA, kappa, p, ncrit, precision, stream, &op->fy))) break;
     const size_t es = precision == FMM_FP64 ? 8 : 4;
     // charges (N) and dipoles (3N); one potential per point and kernel
     if ((rc = balloc(op, &op->q4, 4 * op->N * es))) break;

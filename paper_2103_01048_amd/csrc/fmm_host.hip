@@ -256,35 +256,6 @@ static void kernel_matrix(const std::vector<double> &grid, int n, const double c
   }
 }
 
-// C (m x p, ldc) = A (m x k, lda) * B (k x p, ldb)
-static void matmul_rect(int m, int k, int p, const double *A, int lda, const double *B, int ldb, double *C, int ldc) {
-  std::vector<double> row(p);
-  for (int i = 0; i < m; ++i) {
-    std::fill(row.begin(), row.end(), 0.0);
-    for (int kk = 0; kk < k; ++kk) {
-      const double a = A[(size_t)i * lda + kk];
-      if (a == 0.0) continue;
-      const double *b = B + (size_t)kk * ldb;
-      for (int j = 0; j < p; ++j) row[j] += a * b[j];
-    }
-    std::copy(row.begin(), row.end(), C + (size_t)i * ldc);
-  }
-}
-
-static void matmul(int n, const double *A, const double *B, int ldb, double *C, int ldc) {
-  // C (n x n, ldc) = A (n x n) * B (n x n, ldb)
-  std::vector<double> row(n);
-  for (int i = 0; i < n; ++i) {
-    std::fill(row.begin(), row.end(), 0.0);
-    for (int k = 0; k < n; ++k) {
-      const double a = A[(size_t)i * n + k];
-      const double *b = B + (size_t)k * ldb;
-      for (int j = 0; j < n; ++j) row[j] += a * b[j];
-    }
-    std::copy(row.begin(), row.end(), C + (size_t)i * ldc);
-  }
-}
-
 template <typename F>
 static void parallel_for(int64_t count, F f) {
   unsigned nt = std::max(1u, std::min(32u, std::thread::hardware_concurrency()));
@@ -303,8 +274,11 @@ static void parallel_for(int64_t count, F f) {
 // lane order; the f64 one returns rows lane/16 + 4*reg.  For double, row
 // slot s of the block is fed with row 4*(s%4) + s/4, so that both types
 // leave four consecutive rows in each lane's four result registers.
+// kmajor (the operators of k_m2l, whose lanes read consecutive k of a column
+// at once): column kq*16 + 4*(lane/16) + t instead.
 template <typename T>
-static void swizzle(const double *A, int rows, int cols, int lda, int ld_rows, int Kfull, T *out) {
+static void swizzle(const double *A, int rows, int cols, int lda, int ld_rows, int Kfull, T *out,
+                    bool kmajor = false) {
   const int KQ = Kfull / 16;
   const bool f64 = sizeof(T) == 8;
   for (int rb = 0; rb < ld_rows / 16; ++rb)
@@ -312,7 +286,8 @@ static void swizzle(const double *A, int rows, int cols, int lda, int ld_rows, i
       for (int lane = 0; lane < 64; ++lane)
         for (int t = 0; t < 4; ++t) {
           const int sl = lane & 15;
-          const int i = rb * 16 + (f64 ? 4 * (sl & 3) + (sl >> 2) : sl), k = (kq * 4 + t) * 4 + (lane >> 4);
+          const int i = rb * 16 + (f64 ? 4 * (sl & 3) + (sl >> 2) : sl);
+          const int k = kmajor ? kq * 16 + 4 * (lane >> 4) + t : (kq * 4 + t) * 4 + (lane >> 4);
           const double v = (i < rows && k < cols) ? A[(size_t)i * lda + k] : 0.0;
           out[((size_t)(rb * KQ + kq) * 64 + lane) * 4 + t] = (T)v;
         }
@@ -353,7 +328,8 @@ static void swizzle_bf3(const double *A, int rows, int cols, int lda, int ld_row
 }
 
 template <typename T>
-static int precompute_typed(fmm_plan *P) {
+static int precompute_typed(fmm_plan *P, int set) {
+  OpSet &O = P->ops[set];
   const int p = P->p, n = P->nsurf, ld = P->ld;
   const int yuk = P->kernel == FMM_YUKAWA;
   const int maxl = (int)P->level_begin.size() - 2;
@@ -367,13 +343,21 @@ static int precompute_typed(fmm_plan *P) {
   const double zero[3] = {0, 0, 0};
   auto h_of = [&](int l) { return P->W / (double)(1ll << (l + 1)); };
 
+  // M2L operators of set 0: with singular vectors of one reflection class
+  // each (tsvd_factors_parity), reflecting an offset only flips signs of the
+  // singular coordinates, so the offsets with no negative component serve all
+  // (at most 56 instead of 316 per level).  Set 1 stores every offset.
+  const bool sym = set == 0, fact = P->tune.m2l_factored && !sym;
   std::vector<std::vector<char>> m2l_used(maxl + 1, std::vector<char>(343, 0));
   for (int64_t b = 0; b < (int64_t)P->level.size(); ++b)
     for (int64_t k = P->loff[1][b]; k < P->loff[1][b + 1]; ++k) {
       const int64_t a = P->lidx[1][k];
-      const int c = m2l_code((int)(P->anchor[3 * a] - P->anchor[3 * b]), (int)(P->anchor[3 * a + 1] - P->anchor[3 * b + 1]),
-                             (int)(P->anchor[3 * a + 2] - P->anchor[3 * b + 2]));
-      m2l_used[P->level[b]][c] = 1;
+      int o[3];
+      for (int d = 0; d < 3; ++d) {
+        o[d] = (int)(P->anchor[3 * a + d] - P->anchor[3 * b + d]);
+        if (sym) o[d] = std::abs(o[d]);
+      }
+      m2l_used[P->level[b]][m2l_code(o[0], o[1], o[2])] = 1;
     }
   std::vector<char> has_children(maxl + 1, 0);
   for (int64_t b = 0; b < (int64_t)P->level.size(); ++b)
@@ -409,16 +393,21 @@ static int precompute_typed(fmm_plan *P) {
       if (used) jobs.push_back({6, gl, 0, code});
     }
   }
-  // truncated SVD factors of the check-from-equivalent matrices
+  // truncated SVD factors of the check-from-equivalent matrices: UT nv x n, VS
+  // n x nv (set 0 leaves some of its columns empty, see tsvd_factors_parity)
+  const int nv = sym ? ld : n;
   std::map<int, std::vector<double>> ut_u, vs_u, ut_d, vs_d;
   std::map<int, int> rk_u, rk_d;
   std::vector<int> svd_levels = glevels;
   if (yuk && maxl >= 2) svd_levels.push_back(maxl + 1);  // never used; keeps l+1 lookups defined
   for (int gl : svd_levels) {
-    ut_u[gl].assign((size_t)n * n, 0); vs_u[gl].assign((size_t)n * n, 0);
-    ut_d[gl].assign((size_t)n * n, 0); vs_d[gl].assign((size_t)n * n, 0);
+    ut_u[gl].assign((size_t)n * nv, 0); vs_u[gl].assign((size_t)n * nv, 0);
+    ut_d[gl].assign((size_t)n * nv, 0); vs_d[gl].assign((size_t)n * nv, 0);
     rk_u[gl] = rk_d[gl] = 0;
   }
+  // reflection classes of the singular vectors (sym), per geometry level
+  std::map<int, std::vector<unsigned char>> cls_u, cls_d;
+  for (int gl : svd_levels) { cls_u[gl].assign(ld, 255); cls_d[gl].assign(ld, 255); }
   {
     std::vector<std::pair<int, int>> pj;
     for (int gl : glevels) { pj.push_back({0, gl}); pj.push_back({1, gl}); }
@@ -430,16 +419,17 @@ static int precompute_typed(fmm_plan *P) {
       const int kind = pj[i].first, gl = pj[i].second;
       const double h = gh(gl);
       std::vector<double> Km((size_t)n * n);
-      if (kind == 0) {
-        kernel_matrix(grid, n, zero, ALPHA_UC * h, zero, ALPHA_UE * h, yuk, P->kappa, Km.data(), n);
-        ranks[i] = tsvd_factors(n, Km.data(), tau, ut_u[gl].data(), vs_u[gl].data(), per_svd);
-      } else {
-        kernel_matrix(grid, n, zero, ALPHA_DC * h, zero, ALPHA_DE * h, yuk, P->kappa, Km.data(), n);
-        ranks[i] = tsvd_factors(n, Km.data(), tau, ut_d[gl].data(), vs_d[gl].data(), per_svd);
-      }
+      if (kind == 0) kernel_matrix(grid, n, zero, ALPHA_UC * h, zero, ALPHA_UE * h, yuk, P->kappa, Km.data(), n);
+      else kernel_matrix(grid, n, zero, ALPHA_DC * h, zero, ALPHA_DE * h, yuk, P->kappa, Km.data(), n);
+      double *ut = (kind == 0 ? ut_u : ut_d).at(gl).data(), *vs = (kind == 0 ? vs_u : vs_d).at(gl).data();
+      ranks[i] = sym ? tsvd_factors_parity(n, grid.data(), Km.data(), tau, ut, vs, nv,
+                                           (kind == 0 ? cls_u : cls_d).at(gl).data())
+                     : tsvd_factors(n, Km.data(), tau, ut, vs, per_svd);
     });
     for (size_t i = 0; i < pj.size(); ++i) (pj[i].first == 0 ? rk_u : rk_d)[pj[i].second] = ranks[i];
   }
+  // columns in use: the rank, or (set 0) its 16-wide blocks
+  auto ext = [&](int r) { return sym ? (r + 15) / 16 * 16 : r; };
   auto r16 = [](int r) { return std::max(16, ((r + 15) / 16) * 16); };
   // the child level of a geometry level (Laplace: the unit level itself,
   // with the child factors scaled by 1/2 below)
@@ -449,7 +439,6 @@ static int precompute_typed(fmm_plan *P) {
   for (size_t j = 0; j < jobs.size(); ++j) id1[j] = (int)c1++;
   // factored M2L: each M2L job also stores its right factor R (id1 then holds
   // the left factor L); rank per job
-  const bool fact = P->tune.m2l_factored != 0;
   std::vector<int> idr(jobs.size(), -1), rankf(jobs.size(), 0);
   if (fact)
     for (size_t j = 0; j < jobs.size(); ++j)
@@ -475,21 +464,21 @@ static int precompute_typed(fmm_plan *P) {
     const double h = gh(jb.l);
     T *dst = pool1.data() + id1[j] * m1;
     switch (jb.kind) {
-      case 0: swizzle<T>(ut_u[jb.l].data(), n, n, n, ld, ld, dst); break;
-      case 1: swizzle<T>(vs_u[jb.l].data(), n, n, n, ld, ld, dst); break;
-      case 2: swizzle<T>(ut_d[jb.l].data(), n, n, n, ld, ld, dst); break;
-      case 3: swizzle<T>(vs_d[jb.l].data(), n, n, n, ld, ld, dst); break;
+      case 0: swizzle<T>(ut_u[jb.l].data(), nv, n, n, ld, ld, dst); break;
+      case 1: swizzle<T>(vs_u[jb.l].data(), n, nv, nv, ld, ld, dst); break;
+      case 2: swizzle<T>(ut_d[jb.l].data(), nv, n, n, ld, ld, dst); break;
+      case 3: swizzle<T>(vs_d[jb.l].data(), n, nv, nv, ld, ld, dst); break;
       case 4: {
         // octant c: parent singular coordinates from the child's
         const int cl = child_of(jb.l);
-        const int rp = rk_u[jb.l], rc = rk_u[cl];
+        const int rp = ext(rk_u[jb.l]), rc = ext(rk_u[cl]);
         const double cs = jb.l < 0 ? 0.5 : 1.0;  // Laplace: child V S^-1 at half the unit size
         const int c = jb.oct;
         std::vector<double> Km((size_t)n * n), KV((size_t)n * rc), M((size_t)rp * rc);
         const double off[3] = {(((c >> 2) & 1) ? 0.5 : -0.5) * h, (((c >> 1) & 1) ? 0.5 : -0.5) * h,
                                ((c & 1) ? 0.5 : -0.5) * h};
         kernel_matrix(grid, n, zero, ALPHA_UC * h, off, ALPHA_UE * h * 0.5, yuk, P->kappa, Km.data(), n);
-        matmul_rect(n, n, rc, Km.data(), n, vs_u[cl].data(), n, KV.data(), rc);
+        matmul_rect(n, n, rc, Km.data(), n, vs_u[cl].data(), nv, KV.data(), rc);
         matmul_rect(rp, n, rc, ut_u[jb.l].data(), n, KV.data(), rc, M.data(), rc);
         for (double &v : M) v *= cs;
         swizzle<T>(M.data(), rp, rc, rc, ld, ld, dst);
@@ -498,12 +487,12 @@ static int precompute_typed(fmm_plan *P) {
       case 5: {
         const int cl = child_of(jb.l);
         const int c = jb.oct;
-        const int rp = rk_d[jb.l], rc = rk_d[cl];
+        const int rp = ext(rk_d[jb.l]), rc = ext(rk_d[cl]);
         const double off[3] = {(((c >> 2) & 1) ? 0.5 : -0.5) * h, (((c >> 1) & 1) ? 0.5 : -0.5) * h,
                                ((c & 1) ? 0.5 : -0.5) * h};
         std::vector<double> Km((size_t)n * n), KV((size_t)n * rp), M((size_t)rc * rp);
         kernel_matrix(grid, n, off, ALPHA_DC * h * 0.5, zero, ALPHA_DE * h, yuk, P->kappa, Km.data(), n);
-        matmul_rect(n, n, rp, Km.data(), n, vs_d[jb.l].data(), n, KV.data(), rp);
+        matmul_rect(n, n, rp, Km.data(), n, vs_d[jb.l].data(), nv, KV.data(), rp);
         matmul_rect(rc, n, rp, ut_d[cl].data(), n, KV.data(), rp, M.data(), rp);
         swizzle<T>(M.data(), rc, rp, rp, ld, ld, dst);
         break;
@@ -511,10 +500,10 @@ static int precompute_typed(fmm_plan *P) {
       default: {
         const int code = jb.code;
         const double o[3] = {2.0 * h * (code / 49 - 3), 2.0 * h * ((code / 7) % 7 - 3), 2.0 * h * (code % 7 - 3)};
-        const int ru = rk_u[jb.l], rd = rk_d[jb.l];
+        const int ru = ext(rk_u[jb.l]), rd = ext(rk_d[jb.l]);
         std::vector<double> Km((size_t)n * n), KV((size_t)n * ru), M((size_t)rd * ru);
         kernel_matrix(grid, n, zero, ALPHA_DC * h, o, ALPHA_UE * h, yuk, P->kappa, Km.data(), n);
-        matmul_rect(n, n, ru, Km.data(), n, vs_u[jb.l].data(), n, KV.data(), ru);
+        matmul_rect(n, n, ru, Km.data(), n, vs_u[jb.l].data(), nv, KV.data(), ru);
         matmul_rect(rd, n, ru, ut_d[jb.l].data(), n, KV.data(), ru, M.data(), ru);
         if (fact) {
           // M ~ L R (rank k): L (rd x k) where the operator was, R (k x ru)
@@ -529,7 +518,7 @@ static int precompute_typed(fmm_plan *P) {
             swizzle_bf3(Rf.data(), kf, ru, ru, ld, KB, poolbf.data() + idbfr[j] * mbf);
           }
         } else {
-          swizzle<T>(M.data(), rd, ru, ru, ld, ld, dst);
+          swizzle<T>(M.data(), rd, ru, ru, ld, ld, dst, sym);
           if (idbf[j] >= 0) swizzle_bf3(M.data(), rd, ru, ru, ld, KB, poolbf.data() + idbf[j] * mbf);
         }
       }
@@ -539,51 +528,87 @@ static int precompute_typed(fmm_plan *P) {
   // so V S^-1 at level l is h_l times the unit factor; M2M, L2L and M2L in
   // singular coordinates are scale-free.
   const int L1 = maxl + 1;
-  P->utu_id.assign(L1, -1); P->vsu_id.assign(L1, -1); P->utd_id.assign(L1, -1); P->vsd_id.assign(L1, -1);
-  P->rank_u.assign(L1 + 1, 0); P->rank_d.assign(L1 + 1, 0);
-  P->m2m_id.assign(L1, std::vector<int>(8, -1));
-  P->l2l_id.assign(L1, std::vector<int>(8, -1));
-  P->m2l_id.assign(L1, std::vector<int>(343, -1));
-  P->m2l_r_id.assign(L1, std::vector<int>(343, -1));
-  P->m2l_k.assign(L1, std::vector<int>(343, 0));
-  P->vs_alpha.assign(L1, 1); P->k_alpha.assign(L1, 1);
+  O.utu_id.assign(L1, -1); O.vsu_id.assign(L1, -1); O.utd_id.assign(L1, -1); O.vsd_id.assign(L1, -1);
+  O.rank_u.assign(L1 + 1, 0); O.rank_d.assign(L1 + 1, 0);
+  O.m2m_id.assign(L1, std::vector<int>(8, -1));
+  O.l2l_id.assign(L1, std::vector<int>(8, -1));
+  O.m2l_id.assign(L1, std::vector<int>(343, -1));
+  O.m2l_r_id.assign(L1, std::vector<int>(343, -1));
+  O.m2l_k.assign(L1, std::vector<int>(343, 0));
+  O.vs_alpha.assign(L1, 1);
   for (int l = 2; l <= maxl; ++l) {
     const int gl = yuk ? l : -1;
-    P->rank_u[l] = rk_u[gl];
-    P->rank_d[l] = rk_d[gl];
-    P->vs_alpha[l] = yuk ? 1.0 : h_of(l);
+    O.rank_u[l] = rk_u[gl];
+    O.rank_d[l] = rk_d[gl];
+    O.vs_alpha[l] = yuk ? 1.0 : h_of(l);
   }
   for (size_t j = 0; j < jobs.size(); ++j) {
     const Job &jb = jobs[j];
     for (int l = 2; l <= maxl; ++l) {
       if (jb.l >= 0 && jb.l != l) continue;
       switch (jb.kind) {
-        case 0: P->utu_id[l] = id1[j]; break;
-        case 1: P->vsu_id[l] = id1[j]; break;
-        case 2: P->utd_id[l] = id1[j]; break;
-        case 3: P->vsd_id[l] = id1[j]; break;
-        case 4: P->m2m_id[l][jb.oct] = id1[j]; break;
-        case 5: P->l2l_id[l][jb.oct] = id1[j]; break;
+        case 0: O.utu_id[l] = id1[j]; break;
+        case 1: O.vsu_id[l] = id1[j]; break;
+        case 2: O.utd_id[l] = id1[j]; break;
+        case 3: O.vsd_id[l] = id1[j]; break;
+        case 4: O.m2m_id[l][jb.oct] = id1[j]; break;
+        case 5: O.l2l_id[l][jb.oct] = id1[j]; break;
         case 6:
-          P->m2l_id[l][jb.code] = bf3 ? idbf[j] : id1[j];
-          P->m2l_r_id[l][jb.code] = bf3 ? idbfr[j] : idr[j];
-          P->m2l_k[l][jb.code] = rankf[j];
+          O.m2l_id[l][jb.code] = bf3 ? idbf[j] : id1[j];
+          O.m2l_r_id[l][jb.code] = bf3 ? idbfr[j] : idr[j];
+          O.m2l_k[l][jb.code] = rankf[j];
           break;
       }
     }
   }
-  P->pool1_count = c1;
-  P->m2l_ldt = 0;
+  // sign tables (sym), one byte per singular coordinate: bit m of entry
+  // [side][level][k] (side 0 upward, 1 downward) is the parity of
+  // popcount(class & m), the sign of coordinate k under the reflection m
+  std::vector<unsigned char> par((size_t)2 * L1 * ld, 0);
+  for (int l = 2; l <= maxl; ++l)
+    for (int side = 0; side < 2; ++side) {
+      const std::vector<unsigned char> &cls = (side ? cls_d : cls_u).at(yuk ? l : -1);
+      for (int k = 0; k < ld; ++k)
+        for (int m = 0; m < 8; ++m)
+          if (cls[k] < 8 && (__builtin_popcount(cls[k] & m) & 1))
+            par[((size_t)side * L1 + l) * ld + k] |= (unsigned char)(1 << m);
+    }
+  // zero tiles (sym): an operator whose offset is zero along an axis couples
+  // only coordinates of equal parity in it
+  const int nrb_all = ld / 16;
+  std::vector<uint32_t> tiles((size_t)L1 * 8 * nrb_all, 0);
+  for (int l = 2; l <= maxl && sym; ++l) {
+    const std::vector<unsigned char> &cd = cls_d.at(yuk ? l : -1), &cu = cls_u.at(yuk ? l : -1);
+    for (int z = 0; z < 8; ++z)
+      for (int i = 0; i < ld; ++i)
+        for (int k = 0; k < ld; ++k)
+          if (cd[i] < 8 && cu[k] < 8 && !((cd[i] ^ cu[k]) & z))
+            tiles[((size_t)l * 8 + z) * nrb_all + i / 16] |= 1u << (k / 16);
+  }
+  O.pool1_count = c1;
+  O.m2l_ldt = 0;
   if (fact) {
     int kmax = 1;
     for (size_t j = 0; j < jobs.size(); ++j) kmax = std::max(kmax, rankf[j]);
-    P->m2l_ldt = ((kmax + 31) / 32) * 32;
+    O.m2l_ldt = ((kmax + 31) / 32) * 32;
   }
   int rc;
-  if ((rc = upload(P, &P->pool1, pool1))) return rc;
-  P->bf_kb = KB;
-  P->poolbf_count = cbf;
-  if (bf3 && (rc = upload(P, &P->pool_bf, poolbf))) return rc;
+  if ((rc = upload(P, &O.pool1, pool1))) return rc;
+  if (sym && (rc = upload(P, (void **)&O.d_par, par))) return rc;
+  if (sym && (rc = upload(P, (void **)&O.d_tiles, tiles))) return rc;
+  O.bf_kb = KB;
+  O.poolbf_count = cbf;
+  if (bf3 && (rc = upload(P, &O.pool_bf, poolbf))) return rc;
+  O.built = true;
+  return FMM_OK;
+}
+
+// Surface grid and box geometry.
+template <typename T>
+static int upload_geometry(fmm_plan *P) {
+  const int n = P->nsurf;
+  const std::vector<double> grid = surface_grid(P->p);
+  int rc;
   // surface grid table (T4)
   std::vector<T> sg((size_t)n * 4);
   for (int i = 0; i < n; ++i) {
@@ -825,51 +850,77 @@ static int upload_lists(fmm_plan *P) {
   if ((rc = upload(P, (void **)&D.x_off, xo))) return rc;
   if ((rc = upload(P, (void **)&D.x_idx, xi))) return rc;
   if ((rc = upload_real(P, &D.x_o, x_o))) return rc;
-  // V pairs in GEMM order, (level, offset code, target): a counting sort over
-  // the 343 offset codes of each level, stable in target order (boxes and
-  // their V lists are visited in order).  vpp gives, per V-list entry in
-  // target-major order (the order of each box's sum: its V list, ascending
-  // source id), the pair's position in GEMM order.
+  // M2L columns: one per (target box, source parent), holding the parent's
+  // children on the target's V list as up to eight k segments, so that one
+  // GEMM column sums them and the sum per target runs over source parents
+  // (about 4.5 times fewer than V pairs on a surface).  A column's shape is,
+  // per axis, the parent offset d and the target's child bit t (208 shapes);
+  // its sources sit at offsets 2 d + s - t, s their child bits.  Reflections
+  // reduce the shapes to 26: an axis is flipped when d < 0 or (d = 0 and
+  // t = 1), which leaves (d, t) = (0, 0), (1, 0) or (1, 1) and offsets >= 0.
+  // A counting sort orders the columns by (level, shape, Gray code of the
+  // children present), so that the columns of one 16-wide MFMA block mostly
+  // hold the same children.
   {
-    const int64_t nv = P->loff[1][nb];
-    const int nbucket = (MAXLEVEL + 1) * 343;
-    std::vector<int32_t> bucket((size_t)nv);
-    std::vector<int64_t> cursor((size_t)nbucket + 1, 0);
-    for (int64_t b = 0; b < nb; ++b)
-      for (int64_t k = P->loff[1][b]; k < P->loff[1][b + 1]; ++k) {
-        const int64_t a = P->lidx[1][k];
-        const int c = m2l_code((int)(P->anchor[3 * a] - P->anchor[3 * b]),
-                               (int)(P->anchor[3 * a + 1] - P->anchor[3 * b + 1]),
-                               (int)(P->anchor[3 * a + 2] - P->anchor[3 * b + 2]));
-        bucket[k] = P->level[b] * 343 + c;
-        cursor[bucket[k] + 1]++;
-      }
-    for (int i = 0; i < nbucket; ++i) cursor[i + 1] += cursor[i];
-    P->vpair_src.resize((size_t)nv);
-    P->vpair_tgt.resize((size_t)nv);
-    std::vector<int32_t> vpp((size_t)nv);
-    for (int64_t b = 0; b < nb; ++b)
-      for (int64_t k = P->loff[1][b]; k < P->loff[1][b + 1]; ++k) {
-        const int64_t pos = cursor[bucket[k]]++;
-        P->vpair_src[pos] = (int32_t)P->lidx[1][k];
-        P->vpair_tgt[pos] = (int32_t)b;
-        vpp[k] = (int32_t)pos;
-      }
-    // every box at level >= 2 gets its sum (possibly empty); those boxes
-    // are the last ones (boxes are ordered by level) and hold every V entry
-    std::vector<int32_t> vt, vo;
+    struct Col { int32_t tgt; int32_t src[8]; int32_t key; uint8_t flip; };
+    std::vector<Col> cols;
     const int64_t b2 = P->level_begin.size() > 2 ? P->level_begin[2] : nb;
-    for (int64_t b = b2; b < nb; ++b) {
-      vt.push_back((int32_t)b);
-      vo.push_back((int32_t)(P->loff[1][b] - P->loff[1][b2]));
-    }
-    vo.push_back((int32_t)(P->loff[1][nb] - P->loff[1][b2]));
     if (P->loff[1][b2] != 0) {
       set_error("internal: V lists above level 2");
       return FMM_EINVAL;
     }
+    std::vector<int32_t> vt, vo;
+    std::vector<int64_t> cursor((size_t)(MAXLEVEL + 1) * 27 * 256 + 1, 0);
+    for (int64_t b = b2; b < nb; ++b) {
+      vt.push_back((int32_t)b);
+      vo.push_back((int32_t)cols.size());
+      for (int64_t k = P->loff[1][b]; k < P->loff[1][b + 1];) {
+        const int64_t pa = P->parent[P->lidx[1][k]], pb = P->parent[b];
+        Col c;
+        c.tgt = (int32_t)b;
+        c.flip = 0;
+        std::fill(c.src, c.src + 8, -1);
+        int shape = 0;
+        for (int d = 0; d < 3; ++d) {
+          int64_t off = P->anchor[3 * pa + d] - P->anchor[3 * pb + d];
+          int t = (int)(P->anchor[3 * b + d] & 1);
+          if (off < 0 || (off == 0 && t == 1)) {
+            c.flip |= (uint8_t)(4 >> d);
+            off = -off;
+            t ^= 1;
+          }
+          shape = shape * 3 + (off == 0 ? 0 : 1 + t);
+        }
+        int mask = 0;
+        for (; k < P->loff[1][b + 1] && P->parent[P->lidx[1][k]] == pa; ++k) {
+          const int64_t a = P->lidx[1][k];
+          int oct = (int)(((P->anchor[3 * a] & 1) << 2) | ((P->anchor[3 * a + 1] & 1) << 1) | (P->anchor[3 * a + 2] & 1));
+          oct ^= c.flip;
+          c.src[oct] = (int32_t)a;
+          mask |= 1 << oct;
+        }
+        c.key = (P->level[b] * 27 + shape) * 256 + (mask ^ (mask >> 1));
+        cursor[c.key + 1]++;
+        cols.push_back(c);
+      }
+    }
+    vo.push_back((int32_t)cols.size());
+    for (size_t i = 1; i < cursor.size(); ++i) cursor[i] += cursor[i - 1];
+    const int64_t nc = (int64_t)cols.size();
+    P->mcol_src.resize((size_t)nc * 8);
+    P->mcol_key.resize((size_t)nc);
+    P->mcol_flip.resize((size_t)nc);
+    std::vector<int32_t> vpp((size_t)nc);
+    for (int64_t i = 0; i < nc; ++i) {
+      const int64_t pos = cursor[cols[i].key]++;
+      std::copy(cols[i].src, cols[i].src + 8, &P->mcol_src[(size_t)pos * 8]);
+      P->mcol_key[pos] = cols[i].key / 256;
+      P->mcol_flip[pos] = cols[i].flip;
+      vpp[i] = (int32_t)pos;
+    }
+    // every box at level >= 2 gets its sum (possibly empty)
     D.nvbox = (int)vt.size();
-    D.nvpair = nv;
+    D.nvcol = nc;
     if ((rc = upload(P, (void **)&D.v_tgt, vt))) return rc;
     if ((rc = upload(P, (void **)&D.v_off, vo))) return rc;
     if ((rc = upload(P, (void **)&D.v_pair, vpp))) return rc;
@@ -897,14 +948,14 @@ static int upload_lists(fmm_plan *P) {
 
 static void add_columns(GemmBatch &bt, int mat, double alpha, const std::vector<int32_t> &src,
                         const std::vector<int32_t> &dst) {
-  // src has S entries per column; split into tasks of bt.nt columns
+  // src has S entries per column; split into tasks of GEMM_NT columns
   const int nc = (int)dst.size();
   const int base = (int)bt.h_dst.size();
-  for (int c0 = 0; c0 < nc; c0 += bt.nt) {
+  for (int c0 = 0; c0 < nc; c0 += GEMM_NT) {
     GemmTask t;
     t.mat = mat;
     t.col0 = base + c0;
-    t.ncol = std::min(bt.nt, nc - c0);
+    t.ncol = std::min(GEMM_NT, nc - c0);
     t.nrb = 0;
     t.klen = 0;
     t.alpha = alpha;
@@ -915,7 +966,7 @@ static void add_columns(GemmBatch &bt, int mat, double alpha, const std::vector<
 }
 
 static int finish_batch(fmm_plan *P, GemmBatch &bt) {
-  const int64_t nmat = bt.pool == 0 ? P->pool1_count : P->poolbf_count;
+  const int64_t nmat = bt.pool == 0 ? P->ops[bt.set].pool1_count : P->ops[bt.set].poolbf_count;
   for (const GemmTask &t : bt.h_tasks)
     if (t.mat < 0 || t.mat >= nmat) {
       set_error("internal: GEMM task references a missing operator");
@@ -935,15 +986,219 @@ static int finish_batch(fmm_plan *P, GemmBatch &bt) {
 
 // Row length of the M2L pair slots: the largest downward rank, rounded up to
 // 16 (the rows the M2L GEMM computes).
-static int pair_ld(const fmm_plan *P) {
+static int pair_ld(const fmm_plan *P, int set) {
+  const OpSet &O = P->ops[set];
   int m = 16;
-  for (int l = 2; l <= P->dt.maxlevel; ++l) m = std::max(m, std::max(16, ((P->rank_d[l] + 15) / 16) * 16));
+  for (int l = 2; l <= P->dt.maxlevel; ++l) m = std::max(m, std::max(16, ((O.rank_d[l] + 15) / 16) * 16));
   return m;
 }
 
-int ensure_lists(fmm_plan *P, int nr) {
-  PassLists &L = P->lists_by_nr[nr];
+static int r16(int r) { return std::max(16, ((r + 15) / 16) * 16); }
+// k extent of an M2L operator of rank r (the bf16x3 kernels step k by 32)
+static int kround(const fmm_plan *P, int r) {
+  return P->precision == FMM_FP32_BF16X3 ? ((r16(r) + 31) / 32) * 32 : r16(r);
+}
+
+// Tasks of the segmented M2L: up to nt columns of one (level, shape), with the
+// segments that any of them holds.  Few columns (small clouds) run in
+// 16-column tasks, so that the launch has workgroups for the compute units.
+static int m2l_columns(fmm_plan *P, int nr) {
+  const OpSet &O = P->ops[0];
+  PassLists &L = P->lists[0][nr];
+  const int maxl = P->dt.maxlevel;
+  const int64_t nc = P->dt.nvcol;
+  int rc, maxrd = 16;
+  for (int l = 2; l <= maxl; ++l) maxrd = std::max(maxrd, r16(O.rank_d[l]));
+  M2LBatch &M = L.m2lc;
+  M = M2LBatch();
+  int64_t wide = 0;
+  for (int64_t i = 0, j; i < nc; i = j) {
+    for (j = i; j < nc && P->mcol_key[j] == P->mcol_key[i]; ++j) {}
+    wide += ((j - i) * nr + GEMM_NT - 1) / GEMM_NT;
+  }
+  // (measured, 16 against wide columns: 600 points FP32 26.6 against 28.9 us, 8k
+  // and 6k points FP64 45.5 / 52.8 against 56.1 / 72.9 us; 42k points bf16x3,
+  // 192 wide tasks per plan, 70.8 against 44.0 us)
+  M.nt = wide < M2L_WIDE_TASKS ? 16 : P->precision == FMM_FP64 ? 32 : P->precision == FMM_FP32 ? GEMM_NT : P->tune.m2l_cols;
+  M.nrb = maxrd / 16;
+  for (int l = 2; l <= maxl; ++l) M.nrbk = std::max(M.nrbk, r16(O.rank_u[l]) / 16);
+  M.ldy = pair_ld(P, 0);
+  std::vector<M2LTask> tasks;
+  std::vector<int32_t> msrc;
+  struct Group { int64_t cost; int level, first, count; };
+  std::vector<Group> groups;
+  for (int64_t i = 0, j; i < nc; i = j) {
+    const int l = P->mcol_key[i] / 27, shape = P->mcol_key[i] % 27;
+    for (j = i; j < nc && P->mcol_key[j] == P->mcol_key[i]; ++j) {}
+    groups.push_back({0, l, (int)tasks.size(), 0});
+    const int sh[3] = {shape / 9, (shape / 3) % 3, shape % 3};
+    for (int64_t c0 = i * nr; c0 < j * nr; c0 += M.nt) {
+      M2LTask t;
+      std::memset(&t, 0, sizeof(t));
+      t.col0 = (int32_t)c0;
+      t.ncol = (int32_t)std::min<int64_t>(M.nt, j * nr - c0);
+      t.nrb = r16(O.rank_d[l]) / 16;
+      t.klen = kround(P, O.rank_u[l]);
+      t.tab = l;
+      if (c0 > 0x7fffffff - M.nt || msrc.size() > 0x7fffffffu - 8 * (size_t)M.nt) {
+        set_error("too many V pairs");
+        return FMM_EINVAL;
+      }
+      t.src0 = (int32_t)msrc.size();
+      for (int oct = 0; oct < 8; ++oct) {
+        uint32_t blocks = 0;
+        for (int c = 0; c < t.ncol; ++c)
+          if (P->mcol_src[(size_t)((c0 + c) / nr) * 8 + oct] >= 0) blocks |= 1u << (c / 16);
+        if (!blocks) continue;
+        int o[3];
+        for (int d = 0; d < 3; ++d) o[d] = (sh[d] ? 2 : 0) + ((oct >> (2 - d)) & 1) - (sh[d] == 2 ? 1 : 0);
+        t.mat[t.nseg] = O.m2l_id[l][m2l_code(o[0], o[1], o[2])];
+        if (t.mat[t.nseg] < 0) { set_error("internal: M2L task references a missing operator"); return FMM_EINVAL; }
+        t.blocks |= (uint64_t)blocks << (8 * t.nseg);
+        t.zero[t.nseg] = (uint8_t)((o[0] ? 0 : 4) | (o[1] ? 0 : 2) | (o[2] ? 0 : 1));
+        ++t.nseg;
+        for (int c = 0; c < M.nt; ++c) {
+          const int32_t a = c < t.ncol ? P->mcol_src[(size_t)((c0 + c) / nr) * 8 + oct] : -1;
+          msrc.push_back(a < 0 ? -1 : a * nr + (int32_t)((c0 + c) % nr));
+        }
+      }
+      groups.back().cost += (int64_t)t.nseg * t.nrb * t.klen;
+      ++groups.back().count;
+      tasks.push_back(t);
+    }
+  }
+  // launch order: the shapes whose tasks are longest first (a short last round
+  // of workgroups), the levels of the two M2L launches of m2l_early apart
+  const int ls = std::max(2, maxl - 1);
+  for (Group &gr : groups) gr.cost /= gr.count;
+  std::stable_sort(groups.begin(), groups.end(), [&](const Group &a, const Group &b) {
+    return (a.level >= ls) != (b.level >= ls) ? a.level < ls : a.cost > b.cost;
+  });
+  std::vector<M2LTask> ordered;
+  M.split = 0;
+  for (const Group &gr : groups) {
+    ordered.insert(ordered.end(), tasks.begin() + gr.first, tasks.begin() + gr.first + gr.count);
+    if (gr.level < ls) M.split = (int)ordered.size();
+  }
+  M.ntask = (int)ordered.size();
+  if ((rc = upload(P, (void **)&M.d_tasks, ordered))) return rc;
+  if ((rc = upload(P, (void **)&M.d_src, msrc))) return rc;
+  std::vector<uint8_t> mflip((size_t)(nc * nr));
+  for (int64_t c = 0; c < nc * nr; ++c) mflip[c] = P->mcol_flip[c / nr];
+  if ((rc = upload(P, (void **)&M.d_flip, mflip))) return rc;
+  return FMM_OK;
+}
+
+// V pairs by (level, offset code), a counting sort stable in target order:
+// vpair_src the sources in that order, vpair_first the first pair of each
+// (level, code), vpair_pos the position of each V-list entry.
+static void sort_pairs(fmm_plan *P) {
+  const int64_t nb = (int64_t)P->level.size(), np = P->loff[1][nb];
+  std::vector<int32_t> bucket((size_t)np);
+  std::vector<int64_t> cursor((size_t)(MAXLEVEL + 1) * 343 + 1, 0);
+  for (int64_t b = 0; b < nb; ++b)
+    for (int64_t k = P->loff[1][b]; k < P->loff[1][b + 1]; ++k) {
+      const int64_t a = P->lidx[1][k];
+      bucket[k] = P->level[b] * 343 + m2l_code((int)(P->anchor[3 * a] - P->anchor[3 * b]),
+                                               (int)(P->anchor[3 * a + 1] - P->anchor[3 * b + 1]),
+                                               (int)(P->anchor[3 * a + 2] - P->anchor[3 * b + 2]));
+      cursor[bucket[k] + 1]++;
+    }
+  for (size_t i = 1; i < cursor.size(); ++i) cursor[i] += cursor[i - 1];
+  P->vpair_first = cursor;
+  P->vpair_src.resize((size_t)np);
+  P->vpair_pos.resize((size_t)np);
+  for (int64_t k = 0; k < np; ++k) {
+    const int64_t pos = cursor[bucket[k]]++;
+    P->vpair_src[pos] = (int32_t)P->lidx[1][k];
+    P->vpair_pos[k] = (int32_t)pos;
+  }
+}
+
+// Tasks of the pairwise M2L: V pairs by (level, offset), in target order, each
+// with its own slot, summed per target in V-list order.
+static int m2l_pairs(fmm_plan *P, int nr) {
+  const OpSet &O = P->ops[1];
+  PassLists &L = P->lists[1][nr];
+  const int maxl = P->dt.maxlevel;
+  const int64_t nb = (int64_t)P->level.size(), np = P->loff[1][nb];
+  const bool fact = P->tune.m2l_factored != 0;
+  int rc, maxru = 16, maxrd = 16;
+  for (int l = 2; l <= maxl; ++l) { maxru = std::max(maxru, r16(O.rank_u[l])); maxrd = std::max(maxrd, r16(O.rank_d[l])); }
+  L.m2l = GemmBatch();
+  L.m2l_r = GemmBatch();
+  L.m2l.set = L.m2l_r.set = 1;
+  L.m2l.nrb = maxrd / 16; L.m2l.klen = maxru; L.m2l.ldy = pair_ld(P, 1);
+  if (P->precision == FMM_FP32_BF16X3) {
+    L.m2l.pool = 2;
+    L.m2l.klen = std::min(((maxru + 31) / 32) * 32, O.bf_kb * 32);
+  }
+  if (fact) {
+    // R maps upward coordinates (k <= maxru) to intermediates of m2l_ldt
+    // values per pair; L reads those rows
+    L.m2l_r.pool = L.m2l.pool;
+    L.m2l_r.klen = L.m2l.klen;
+    L.m2l_r.nrb = O.m2l_ldt / 16;
+    L.m2l_r.ldy = O.m2l_ldt;
+    L.m2l.ldx = O.m2l_ldt;
+    L.m2l.klen = O.m2l_ldt;
+  }
+  if (P->vpair_first.empty()) sort_pairs(P);
+  const std::vector<int64_t> &first = P->vpair_first;
+  std::vector<int32_t> src, dst;
+  L.m2l_t0.assign((size_t)maxl + 2, -1);
+  for (int gi = 0; gi < (maxl + 1) * 343; ++gi) {
+    if (first[gi] == first[gi + 1]) continue;
+    const int l = gi / 343, code = gi % 343;
+    if (L.m2l_t0[l] < 0) L.m2l_t0[l] = (int)L.m2l.h_tasks.size();
+    src.clear(); dst.clear();
+    for (int64_t j = first[gi]; j < first[gi + 1]; ++j)
+      for (int r = 0; r < nr; ++r) {
+        src.push_back((int32_t)(P->vpair_src[j] * nr + r));
+        dst.push_back((int32_t)(j * nr + r));
+      }
+    // only the rows of this level's downward rank and the columns of its
+    // upward rank (the rest of the operator is zero padding)
+    const int kf = fact ? O.m2l_k[l][code] : O.rank_u[l];
+    if (fact) {
+      const size_t t0 = L.m2l_r.h_tasks.size();
+      add_columns(L.m2l_r, O.m2l_r_id[l][code], 1.0, src, dst);
+      for (size_t t = t0; t < L.m2l_r.h_tasks.size(); ++t) {
+        L.m2l_r.h_tasks[t].nrb = r16(kf) / 16;
+        L.m2l_r.h_tasks[t].klen = kround(P, O.rank_u[l]);
+      }
+    }
+    const size_t t0 = L.m2l.h_tasks.size();
+    add_columns(L.m2l, O.m2l_id[l][code], 1.0, fact ? dst : src, dst);
+    for (size_t t = t0; t < L.m2l.h_tasks.size(); ++t) {
+      L.m2l.h_tasks[t].nrb = r16(O.rank_d[l]) / 16;
+      L.m2l.h_tasks[t].klen = kround(P, kf);
+    }
+  }
+  L.m2l_t0[maxl + 1] = (int)L.m2l.h_tasks.size();
+  for (int l = maxl; l >= 0; --l)
+    if (L.m2l_t0[l] < 0) L.m2l_t0[l] = L.m2l_t0[l + 1];
+  if ((rc = finish_batch(P, L.m2l))) return rc;
+  if (fact && (rc = finish_batch(P, L.m2l_r))) return rc;
+  if (!P->d_vp_off) {
+    std::vector<int32_t> off;
+    const int64_t b2 = P->level_begin.size() > 2 ? P->level_begin[2] : nb;
+    for (int64_t b = b2; b <= nb; ++b) off.push_back((int32_t)P->loff[1][b]);
+    if ((rc = upload(P, (void **)&P->d_vp_off, off))) return rc;
+    if ((rc = upload(P, (void **)&P->d_vp_pair, P->vpair_pos))) return rc;
+  }
+  return FMM_OK;
+}
+
+int ensure_lists(fmm_plan *P, int nr, int set) {
+  const OpSet &O = P->ops[set];
+  PassLists &L = P->lists[set][nr];
   if (L.nr == nr) return FMM_OK;
+  if (P->n > 0 && !O.built) {
+    // an operator's plan evaluated in another way than its operator does
+    const int e = P->precision == FMM_FP64 ? precompute_typed<double>(P, set) : precompute_typed<float>(P, set);
+    if (e) return e;
+  }
   const int maxl = P->dt.maxlevel;
   const int ld = P->ld;
   const int64_t nb = (int64_t)P->level.size();
@@ -958,37 +1213,19 @@ int ensure_lists(fmm_plan *P, int nr) {
         dst.push_back((int32_t)(boxes_dst[i] * nr + r));
       }
   };
-  auto r16 = [](int r) { return std::max(16, ((r + 15) / 16) * 16); };
   auto oct_of = [&](int64_t b) {
     return (int)(((P->anchor[3 * b] & 1) << 2) | ((P->anchor[3 * b + 1] & 1) << 1) | (P->anchor[3 * b + 2] & 1));
   };
   int maxru = 16, maxrd = 16;
-  for (int l = 2; l <= maxl; ++l) { maxru = std::max(maxru, r16(P->rank_u[l])); maxrd = std::max(maxrd, r16(P->rank_d[l])); }
+  for (int l = 2; l <= maxl; ++l) { maxru = std::max(maxru, r16(O.rank_u[l])); maxrd = std::max(maxrd, r16(O.rank_d[l])); }
   const int L1 = std::max(maxl + 1, 0);
   L.m2m.assign(L1, GemmBatch()); L.l2l.assign(L1, GemmBatch());
-  L.ut_u_all = GemmBatch(); L.vs_u = GemmBatch(); L.ut_dx = GemmBatch(); L.vs_d = GemmBatch(); L.m2l = GemmBatch();
+  L.ut_u_all = GemmBatch(); L.vs_u = GemmBatch(); L.ut_dx = GemmBatch(); L.vs_d = GemmBatch();
+  L.ut_u_all.set = L.vs_u.set = L.ut_dx.set = L.vs_d.set = set;
   L.ut_u_all.nrb = maxru / 16; L.ut_u_all.klen = ld;
   L.vs_u.nrb = ld / 16; L.vs_u.klen = maxru;
   L.ut_dx.nrb = maxrd / 16; L.ut_dx.klen = ld;
   L.vs_d.nrb = ld / 16; L.vs_d.klen = maxrd;
-  L.m2l.nrb = maxrd / 16; L.m2l.klen = maxru; L.m2l.ldy = pair_ld(P);
-  if (P->precision == FMM_FP32_BF16X3) {
-    L.m2l.pool = 2;
-    L.m2l.klen = std::min(((maxru + 31) / 32) * 32, P->bf_kb * 32);
-    if (P->tune.m2l_cols == 2 * GEMM_NT && !P->tune.m2l_factored) L.m2l.nt = 2 * GEMM_NT;
-  }
-  // factored M2L: R maps upward coordinates (k <= maxru) to intermediates of
-  // m2l_ldt values per pair; L reads those rows
-  const bool fact = P->tune.m2l_factored != 0;
-  L.m2l_r = GemmBatch();
-  if (fact) {
-    L.m2l_r.pool = L.m2l.pool;
-    L.m2l_r.klen = L.m2l.klen;
-    L.m2l_r.nrb = P->m2l_ldt / 16;
-    L.m2l_r.ldy = P->m2l_ldt;
-    L.m2l.ldx = P->m2l_ldt;
-    L.m2l.klen = P->m2l_ldt;
-  }
   // boxes whose upward equivalent density is evaluated (M2P sources)
   std::vector<char> need_equ(nb, 0);
   for (int64_t b = 0; b < nb; ++b) {
@@ -1008,33 +1245,35 @@ int ensure_lists(fmm_plan *P, int nr) {
     // octant), summed per parent by k_pair_reduce
     if (l < maxl) {
       GemmBatch &bt = L.m2m[l];
-      bt.nrb = r16(P->rank_u[l]) / 16;
-      bt.klen = r16(P->rank_u[l + 1]);
+      bt.set = set;
+      bt.nrb = r16(O.rank_u[l]) / 16;
+      bt.klen = r16(O.rank_u[l + 1]);
       for (int oct = 0; oct < 8; ++oct) {
         std::vector<int64_t> kids;
         for (int64_t b = P->level_begin[l + 1]; b < P->level_begin[l + 2]; ++b)
           if (oct_of(b) == oct) kids.push_back(b);
         if (kids.empty()) continue;
         cols_for(kids, kids);
-        add_columns(bt, P->m2m_id[l][oct], 1.0, src, dst);
+        add_columns(bt, O.m2m_id[l][oct], 1.0, src, dst);
       }
       if ((rc = finish_batch(P, bt))) return rc;
     }
     // upward: leaves' check potentials to singular coordinates (one batch
     // for every level, launched before the M2M sweep)
     cols_for(leaves, leaves);
-    if (!dst.empty()) add_columns(L.ut_u_all, P->utu_id[l], 1.0, src, dst);
+    if (!dst.empty()) add_columns(L.ut_u_all, O.utu_id[l], 1.0, src, dst);
     // upward equivalent densities of the M2P sources
     std::vector<int64_t> eb;
     for (int64_t b : all) if (need_equ[b]) eb.push_back(b);
     cols_for(eb, eb);
-    if (!dst.empty()) add_columns(L.vs_u, P->vsu_id[l], P->vs_alpha[l], src, dst);
+    if (!dst.empty()) add_columns(L.vs_u, O.vsu_id[l], O.vs_alpha[l], src, dst);
     // downward: L2L between singular coordinates (levels >= 3)
     if (l >= 3) {
       GemmBatch &bt = L.l2l[l];
+      bt.set = set;
       bt.mode = GEMM_ADD;
-      bt.nrb = r16(P->rank_d[l]) / 16;
-      bt.klen = r16(P->rank_d[l - 1]);
+      bt.nrb = r16(O.rank_d[l]) / 16;
+      bt.klen = r16(O.rank_d[l - 1]);
       for (int oct = 0; oct < 8; ++oct) {
         std::vector<int64_t> bs, bd;
         for (int64_t b : all) {
@@ -1044,13 +1283,13 @@ int ensure_lists(fmm_plan *P, int nr) {
         }
         if (bd.empty()) continue;
         cols_for(bs, bd);
-        add_columns(bt, P->l2l_id[l - 1][oct], 1.0, src, dst);
+        add_columns(bt, O.l2l_id[l - 1][oct], 1.0, src, dst);
       }
       if ((rc = finish_batch(P, bt))) return rc;
     }
     // downward equivalent densities of the leaves
     cols_for(leaves, leaves);
-    if (!dst.empty()) add_columns(L.vs_d, P->vsd_id[l], P->vs_alpha[l], src, dst);
+    if (!dst.empty()) add_columns(L.vs_d, O.vsd_id[l], O.vs_alpha[l], src, dst);
   }
   // P2L boxes: their check potentials to singular coordinates (added)
   {
@@ -1063,7 +1302,7 @@ int ensure_lists(fmm_plan *P, int nr) {
       while (j < xb.size() && P->level[xb[j]] == P->level[xb[i]]) ++j;
       std::vector<int64_t> part(xb.begin() + i, xb.begin() + j);
       cols_for(part, part);
-      add_columns(L.ut_dx, P->utd_id[P->level[xb[i]]], 1.0, src, dst);
+      add_columns(L.ut_dx, O.utd_id[P->level[xb[i]]], 1.0, src, dst);
       i = j;
     }
   }
@@ -1071,74 +1310,38 @@ int ensure_lists(fmm_plan *P, int nr) {
   if ((rc = finish_batch(P, L.vs_u))) return rc;
   if ((rc = finish_batch(P, L.ut_dx))) return rc;
   if ((rc = finish_batch(P, L.vs_d))) return rc;
-  // M2L: pairs in GEMM order, tasks split at (level, offset) changes
   {
-    const int64_t np = (int64_t)P->vpair_src.size();
-    auto code_of = [&](int64_t j) {
-      const int64_t t = P->vpair_tgt[j], a = P->vpair_src[j];
-      return m2l_code((int)(P->anchor[3 * a] - P->anchor[3 * t]), (int)(P->anchor[3 * a + 1] - P->anchor[3 * t + 1]),
-                      (int)(P->anchor[3 * a + 2] - P->anchor[3 * t + 2]));
-    };
-    int64_t i = 0;
-    L.m2l_t0.assign((size_t)maxl + 2, -1);
-    while (i < np) {
-      const int l = P->level[P->vpair_tgt[i]];
-      const int code = code_of(i);
-      if (L.m2l_t0[l] < 0) L.m2l_t0[l] = (int)L.m2l.h_tasks.size();
-      int64_t j = i;
-      src.clear(); dst.clear();
-      while (j < np && P->level[P->vpair_tgt[j]] == l && code_of(j) == code) {
-        for (int r = 0; r < nr; ++r) {
-          src.push_back((int32_t)(P->vpair_src[j] * nr + r));
-          dst.push_back((int32_t)(j * nr + r));
-        }
-        ++j;
-      }
-      // only the rows of this level's downward rank and the columns of its
-      // upward rank (the rest of the operator is zero padding; the bf16x3
-      // kernel steps k by 32)
-      auto kround = [&](int r) { return L.m2l.pool == 2 ? ((r16(r) + 31) / 32) * 32 : r16(r); };
-      if (fact) {
-        // R: upward coordinates -> the pair's k-value intermediate (row j);
-        // L: intermediate -> the pair's slot
-        const int kf = P->m2l_k[l][code];
-        std::vector<int32_t> mid(dst);
-        size_t t0 = L.m2l_r.h_tasks.size();
-        add_columns(L.m2l_r, P->m2l_r_id[l][code], 1.0, src, mid);
-        for (size_t t = t0; t < L.m2l_r.h_tasks.size(); ++t) {
-          L.m2l_r.h_tasks[t].nrb = r16(kf) / 16;
-          L.m2l_r.h_tasks[t].klen = kround(P->rank_u[l]);
-        }
-        t0 = L.m2l.h_tasks.size();
-        add_columns(L.m2l, P->m2l_id[l][code], 1.0, mid, dst);
-        for (size_t t = t0; t < L.m2l.h_tasks.size(); ++t) {
-          L.m2l.h_tasks[t].nrb = r16(P->rank_d[l]) / 16;
-          L.m2l.h_tasks[t].klen = kround(kf);
-        }
-      } else {
-        const size_t t0 = L.m2l.h_tasks.size();
-        add_columns(L.m2l, P->m2l_id[l][code], 1.0, src, dst);
-        for (size_t t = t0; t < L.m2l.h_tasks.size(); ++t) {
-          L.m2l.h_tasks[t].nrb = r16(P->rank_d[l]) / 16;
-          L.m2l.h_tasks[t].klen = kround(P->rank_u[l]);
-        }
-      }
-      i = j;
-    }
-  }
-  if (L.m2l_t0.size() != (size_t)maxl + 2) L.m2l_t0.assign((size_t)maxl + 2, -1);
-  L.m2l_t0[maxl + 1] = (int)L.m2l.h_tasks.size();
-  for (int l = maxl; l >= 0; --l)
-    if (L.m2l_t0[l] < 0) L.m2l_t0[l] = L.m2l_t0[l + 1];
-  if ((rc = finish_batch(P, L.m2l))) return rc;
-  if (fact && (rc = finish_batch(P, L.m2l_r))) return rc;
-  if (!P->d_m2l_rows) {
     std::vector<int32_t> rows(std::max<int64_t>(1, nb), 16);
     for (int64_t b = 0; b < nb; ++b)
-      if (P->level[b] >= 2) rows[b] = r16(P->rank_d[P->level[b]]);
-    if ((rc = upload(P, (void **)&P->d_m2l_rows, rows))) return rc;
+      if (P->level[b] >= 2) rows[b] = r16(O.rank_d[P->level[b]]);
+    if ((rc = upload(P, (void **)&L.d_m2l_rows, rows))) return rc;
   }
+  if ((rc = set == 0 ? m2l_columns(P, nr) : m2l_pairs(P, nr))) return rc;
   L.nr = nr;
+  return FMM_OK;
+}
+
+// Slots of the M2L form of an operator set for nr columns.
+int ensure_m2l(fmm_plan *P, int nr, int set) {
+  const size_t es = P->precision == FMM_FP64 ? 8 : 4;
+  int rc;
+  if (set == 1) {
+    if (P->pairbuf_nr >= nr) return FMM_OK;
+    const int64_t np = std::max<int64_t>(1, P->loff[1].back());
+    const int ldt = P->ops[1].m2l_ldt;
+    if ((rc = dev_alloc(P, &P->pairbuf, (size_t)np * nr * pair_ld(P, 1) * es))) return rc;
+    if (ldt > 0 && (rc = dev_alloc(P, &P->m2l_t, (size_t)np * nr * ldt * es))) return rc;
+    P->pairbuf_nr = nr;
+    return FMM_OK;
+  }
+  if (P->colbuf_nr >= nr) return FMM_OK;
+  if (P->precision == FMM_FP32_BF16X3) {
+    const size_t bytes = 2 * ((size_t)P->dt.nbox * nr + 1) * P->ld * 2;
+    if ((rc = dev_alloc(P, &P->cub, bytes))) return rc;
+    FMM_HIP_TRY(hipMemset(P->cub, 0, bytes));
+  }
+  if ((rc = dev_alloc(P, &P->colbuf, (size_t)std::max<int64_t>(1, P->dt.nvcol) * nr * pair_ld(P, 0) * es))) return rc;
+  P->colbuf_nr = nr;
   return FMM_OK;
 }
 
@@ -1255,20 +1458,18 @@ int ensure_work(fmm_plan *P, int nr) {
   if ((rc = dev_alloc(P, &P->chk, wbytes))) return rc;
   if ((rc = dev_alloc(P, &P->eqd, wbytes))) return rc;
   if ((rc = dev_alloc(P, &P->chku, wbytes))) return rc;
-  if ((rc = dev_alloc(P, &P->cu, wbytes))) return rc;
+  // one row more: a zero row for absent M2L sources
+  const size_t cbytes = wbytes + (size_t)P->ld * es;
+  if ((rc = dev_alloc(P, &P->cu, cbytes))) return rc;
   if ((rc = dev_alloc(P, &P->yd, wbytes))) return rc;
   if ((rc = dev_alloc(P, &P->mslot, wbytes))) return rc;
   if ((rc = dev_alloc(P, &P->ydx, wbytes))) return rc;
-  if ((rc = dev_alloc(P, &P->pairbuf, (size_t)std::max<int64_t>(1, P->dt.nvpair) * nr * pair_ld(P) * es))) return rc;
-  if (P->m2l_ldt > 0 &&
-      (rc = dev_alloc(P, &P->m2l_t, (size_t)std::max<int64_t>(1, P->dt.nvpair) * nr * P->m2l_ldt * es)))
-    return rc;
   // padding rows/columns must hold zeros (the GEMM K dimension reads them)
   FMM_HIP_TRY(hipMemset(P->equ, 0, wbytes));
   FMM_HIP_TRY(hipMemset(P->chk, 0, wbytes));
   FMM_HIP_TRY(hipMemset(P->eqd, 0, wbytes));
   FMM_HIP_TRY(hipMemset(P->chku, 0, wbytes));
-  FMM_HIP_TRY(hipMemset(P->cu, 0, wbytes));
+  FMM_HIP_TRY(hipMemset(P->cu, 0, cbytes));
   FMM_HIP_TRY(hipMemset(P->yd, 0, wbytes));
   // rows of boxes without an X list stay zero: the M2L sums add this array
   FMM_HIP_TRY(hipMemset(P->ydx, 0, wbytes));
@@ -1348,10 +1549,10 @@ static fmm_plan *find_tree(const fmm_plan *P) {
 // kappa, order and working type on a tree of the same points, root cube and
 // ncrit (the operators depend on the level sizes and on the offsets the V
 // lists use, not on the leaf items).
-static fmm_plan *find_ops(const fmm_plan *P) {
+static fmm_plan *find_ops(const fmm_plan *P, int sets) {
   std::lock_guard<std::mutex> lock(g_tree_mu);
   for (fmm_plan *A : g_tree_plans)
-    if (A->ops_mem && A->kernel == P->kernel && A->kappa == P->kappa && A->p == P->p &&
+    if (A->ops_mem && !(sets & ~(A->ops[0].built | A->ops[1].built << 1)) && A->kernel == P->kernel && A->kappa == P->kappa && A->p == P->p &&
         A->tune.m2l_factored == P->tune.m2l_factored &&
         A->precision == P->precision && A->coord_hash == P->coord_hash && A->n == P->n &&
         A->mol_off == P->mol_off && A->W == P->W && A->mol_lo == P->mol_lo && A->ncrit == P->ncrit &&
@@ -1363,14 +1564,7 @@ static fmm_plan *find_ops(const fmm_plan *P) {
 
 static void share_ops(fmm_plan *P, const fmm_plan *A) {
   P->ops_mem = A->ops_mem;
-  P->pool1 = A->pool1; P->pool_bf = A->pool_bf;
-  P->pool1_count = A->pool1_count; P->poolbf_count = A->poolbf_count;
-  P->bf_kb = A->bf_kb;
-  P->utu_id = A->utu_id; P->vsu_id = A->vsu_id; P->utd_id = A->utd_id; P->vsd_id = A->vsd_id;
-  P->rank_u = A->rank_u; P->rank_d = A->rank_d;
-  P->m2m_id = A->m2m_id; P->l2l_id = A->l2l_id; P->m2l_id = A->m2l_id;
-  P->m2l_r_id = A->m2l_r_id; P->m2l_k = A->m2l_k; P->m2l_ldt = A->m2l_ldt;
-  P->vs_alpha = A->vs_alpha; P->k_alpha = A->k_alpha;
+  for (int k = 0; k < 2; ++k) P->ops[k] = A->ops[k];
   P->surf = A->surf;
   P->dt.box_geom = A->dt.box_geom;
   P->ops_shared = 1;
@@ -1396,7 +1590,9 @@ static int share_tree(fmm_plan *P, const fmm_plan *A, hipStream_t s) {
   P->level = A->level; P->nchild = A->nchild; P->anchor = A->anchor; P->begin = A->begin; P->end = A->end;
   P->parent = A->parent; P->child_begin = A->child_begin; P->level_begin = A->level_begin; P->mol = A->mol;
   for (int k = 0; k < 4; ++k) { P->loff[k] = A->loff[k]; P->lidx[k] = A->lidx[k]; }
-  P->leaf_ids = A->leaf_ids; P->vpair_src = A->vpair_src; P->vpair_tgt = A->vpair_tgt; P->p2l_boxes = A->p2l_boxes;
+  P->leaf_ids = A->leaf_ids; P->p2l_boxes = A->p2l_boxes;
+  P->vpair_src = A->vpair_src; P->vpair_pos = A->vpair_pos; P->vpair_first = A->vpair_first;
+  P->mcol_src = A->mcol_src; P->mcol_key = A->mcol_key; P->mcol_flip = A->mcol_flip;
   P->p2p_inter = A->p2p_inter; P->far_inter = A->far_inter; P->item_pairs = A->item_pairs;
   P->tree_mem = A->tree_mem;
   P->dt = A->dt;
@@ -1423,8 +1619,10 @@ extern "C" {
 
 const char *fmm_last_error(void) { return g_err.c_str(); }
 
+// products: the plan of a boundary-element operator (monopole + dipole
+// evaluations only, unless the caller takes it out by bem_fmm_plan).
 static int setup_common(const double *xyz_dev, const std::vector<int64_t> &off, int kernel, double kappa, int p,
-                        int ncrit, int precision, fmm_stream_t stream, fmm_plan **out) {
+                        int ncrit, int precision, fmm_stream_t stream, fmm_plan **out, bool products = false) {
   auto t0 = std::chrono::steady_clock::now();
   if (!out) { set_error("fmm_setup: out is NULL"); return FMM_EINVAL; }
   *out = nullptr;
@@ -1556,17 +1754,25 @@ static int setup_common(const double *xyz_dev, const std::vector<int64_t> &off, 
     lap(3);
     }
     P->tree_hash = tree_fingerprint(P);
-    if (fmm_plan *A = find_ops(P)) {
+    const int sets = 1 << op_set(P, true) | (products ? 0 : 1 << op_set(P, false));
+    if (fmm_plan *A = find_ops(P, sets)) {
       // a live plan of the same kernel, kappa, order and working type on the
       // same tree: its operators (they do not depend on the leaf items)
       share_ops(P, A);
     } else {
       P->ops_mem = std::make_shared<SharedAllocs>();
       P->alloc_sink = &P->ops_mem->ptrs;
-      rc = precision == FMM_FP64 ? precompute_typed<double>(P) : precompute_typed<float>(P);
+      // the sets that the plan's evaluations take
+      for (int set = 0; set < 2 && !rc; ++set)
+        if ((sets >> set) & 1) rc = precision == FMM_FP64 ? precompute_typed<double>(P, set) : precompute_typed<float>(P, set);
+      if (!rc) rc = precision == FMM_FP64 ? upload_geometry<double>(P) : upload_geometry<float>(P);
       P->alloc_sink = nullptr;
       if (rc) break;
     }
+    // the task lists of one-column evaluations
+    for (int set = 0; set < 2 && !rc; ++set)
+      if ((sets >> set) & 1) rc = ensure_lists(P, 1, set);
+    if (rc) break;
     hipError_t e = hipStreamSynchronize(s);
     lap(4);
     if (e != hipSuccess) { set_error(std::string("fmm_setup: ") + hipGetErrorString(e)); rc = FMM_EHIP; }
@@ -1583,6 +1789,15 @@ int fmm_setup(const double *xyz_dev, int64_t n, int kernel, double kappa, int p,
   if (n < 0) { set_error("fmm_setup: n out of range"); if (out) *out = nullptr; return FMM_EINVAL; }
   return setup_common(xyz_dev, {0, n}, kernel, kappa, p, ncrit, precision, stream, out);
 }
+
+}  // extern "C"
+namespace fmm {
+int setup_products(const double *xyz_dev, int64_t n, int kernel, double kappa, int p, int ncrit, int precision,
+                   fmm_stream_t stream, fmm_plan **out) {
+  return setup_common(xyz_dev, {0, n}, kernel, kappa, p, ncrit, precision, stream, out, true);
+}
+}  // namespace fmm
+extern "C" {
 
 int fmm_setup_batch(const double *xyz_dev, const int64_t *offsets, int nmol, int kernel, double kappa, int p,
                     int ncrit, int precision, fmm_stream_t stream, fmm_plan **out) {
@@ -1705,8 +1920,9 @@ int fmm_info(const fmm_plan *P, fmm_info_t *o) {
     FMM_HIP_TRY(hipMemcpy(&e, P->chain_ctr + P->chain_ctr_n - 1, sizeof(e), hipMemcpyDeviceToHost));
     o->chain_timeouts = e;
   }
-  for (size_t l = 0; l < P->rank_u.size(); ++l) o->rank_up = std::max(o->rank_up, (int32_t)P->rank_u[l]);
-  for (size_t l = 0; l < P->rank_d.size(); ++l) o->rank_down = std::max(o->rank_down, (int32_t)P->rank_d[l]);
+  const OpSet &O = P->ops[P->ops[op_set(P, false)].built ? op_set(P, false) : 1];
+  for (int r : O.rank_u) o->rank_up = std::max(o->rank_up, (int32_t)r);
+  for (int r : O.rank_d) o->rank_down = std::max(o->rank_down, (int32_t)r);
   return FMM_OK;
 }
 

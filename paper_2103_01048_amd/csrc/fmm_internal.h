@@ -14,6 +14,8 @@ namespace fmm {
 
 constexpr int MAXLEVEL = 21;
 constexpr int GEMM_NT = 64;   // columns per GEMM task (4 MFMA column blocks)
+constexpr int M2L_WIDE_TASKS = 160;  // segmented M2L launches of fewer 64-column tasks use 16-column ones
+constexpr int M2L_FEW_COLUMNS = 1024;
 constexpr int MAX_NR = 4;     // density columns handled by one kernel pass
 
 // Surface radii, in units of the box half-width (upward equivalent, upward
@@ -36,9 +38,24 @@ inline int near_early_items(const fmm_tuning_t &t, int nitems, bool far) {
              ? (int)std::min<int64_t>(nitems, (int64_t)nitems * t.near_early / 1000)
              : 0;
 }
+void matmul_rect(int m, int k, int p, const double *A, int lda, const double *B, int ldb, double *C, int ldc);
 void pinv_tsvd(int n, const double *A, double tau, double *out);
 int tsvd_factors(int n, const double *A, double tau, double *UT, double *VS, int nthreads);
+int tsvd_factors_parity(int n, const double *grid, const double *A, double tau, double *UT, double *VS, int ldv,
+                        unsigned char *code);
 int tsvd_split(int rows, int cols, const double *A, double tau, double *L, int ldl, double *R, int ldr);
+
+// Which operator set an evaluation of plan P takes.  Set 0 (segmented M2L) is
+// the faster one but adds a target's sources in another order than set 1
+// (pairwise M2L).  Set 1 serves the factored operators and, in single
+// precision, the two kinds of evaluation whose results are handed on in
+// double precision (`keeps_order`): one column of one plan (the gradients of
+// autograd.py) and monopole + dipole sources (the boundary-element products).
+// Those keep their order of summation and with it every bit.  Single
+// precision takes set 1 for a few columns too (fewer than M2L_FEW_COLUMNS):
+// its launch spreads V pairs over the chip where the segmented one walks up to
+// eight segments in a few workgroups (600 points: 18.5 against 26.6 us).
+inline int op_set(const fmm_plan *P, bool keeps_order);
 
 #define FMM_HIP_TRY(call)                                                        \
   do {                                                                           \
@@ -73,7 +90,7 @@ struct GemmArgs {
   const int32_t *dst;   // ncols row indices into Y
   const void *X;
   void *Y;
-  int ntask, nrb, klen, ldx, ldy, S, seg, KQ, mode, nt;
+  int ntask, nrb, klen, ldx, ldy, S, seg, KQ, mode;
 };
 
 // A batch of GEMM tasks that can run in one launch (no two tasks write the
@@ -86,9 +103,9 @@ struct GemmBatch {
   int kq_stride = 0;           // 16-wide k groups per stored row block (0: row length / 16)
   int ldy = 0;                 // leading dimension of the output rows (0: the work-array row length)
   int mode = GEMM_STORE;
+  int set = 0;                 // operator set
   int pool = 0;                // 0: matrix pool, 2: bf16x3 split pool
   int ldx = 0;                 // row length of X (0: the work-array row length)
-  int nt = GEMM_NT;            // columns per task (the bf16x3 kernel also takes 2 GEMM_NT)
   int ntask = 0;
   GemmTask *d_tasks = nullptr;
   int32_t *d_src = nullptr;    // ncols*S  (row index into X, already * nr + r)
@@ -97,6 +114,49 @@ struct GemmBatch {
   // host copies kept until upload
   std::vector<GemmTask> h_tasks;
   std::vector<int32_t> h_src, h_dst;
+};
+
+// One workgroup of the segmented M2L (k_m2l): columns col0 .. col0 + ncol - 1
+// (one slot row each) of one (level, shape),
+//   slot[c] = F_c^d sum_{s < nseg} pool[mat[s]] F_c^u X[src[src0 + s * nt + c]],
+// F_c the signs of column c's reflection; a source of -1 is absent.
+struct M2LTask {
+  int32_t col0, ncol, nseg;
+  int32_t nrb;       // 16-row blocks (the level's downward rank)
+  int32_t klen;      // k-values per segment (the level's upward rank)
+  int32_t src0;
+  int32_t tab;       // the level's tables: sign bytes at tab * ld, zero-tile masks at tab * 8 * (ld / 16)
+  int32_t pad;
+  uint64_t blocks;   // bit 8 s + b: some column of 16-column block b holds segment s
+  int32_t mat[8];
+  uint8_t zero[8];   // per segment, the axes along which its offset is zero
+};
+
+// Tasks of the segmented M2L.
+struct M2LBatch {
+  int ntask = 0, nt = GEMM_NT;  // tasks; columns per task
+  int split = 0;                // the first task of the two finest levels
+  int nrb = 0, nrbk = 0;        // most row blocks and 16-wide k groups of a task
+  int ldy = 0;                  // slot row length
+  M2LTask *d_tasks = nullptr;
+  int32_t *d_src = nullptr;     // per task, nseg * nt source rows
+  uint8_t *d_flip = nullptr;    // per column, its reflection (bit 2: x, 1: y, 0: z)
+};
+
+// One plan's half of a segmented M2L launch.
+struct M2LArgs {
+  const M2LTask *tasks;
+  const int32_t *src;
+  const uint8_t *flip;
+  const uint8_t *par_u, *par_d;  // [level][ld] sign bytes of the upward and downward coordinates
+  const uint32_t *tiles;         // [level][zero axes][row block]: bit q set when the 16 x 16 tile of k group q is not zero
+  const void *pool;
+  int64_t mstride;               // one operator, in pool units (elements; uint4 for bf16x3)
+  const void *X;
+  void *Y;
+  int64_t xlo;                   // bf16x3: from the high to the low parts in X
+  // nrbk: 16-wide k groups of the largest klen; rbg: row blocks per grid row; zrow: a zero row of X
+  int ntask, nrb, nrbk, rbg, ldx, ldy, zrow, kstride;  // kstride: 16-wide (bf16x3: 32-wide) k groups per stored row block
 };
 
 // Per-nrhs-chunk task lists.  Row indices in the work arrays are
@@ -116,6 +176,32 @@ struct Chain {
   void *tasks = nullptr, *gargs = nullptr, *rargs = nullptr, *need = nullptr;
 };
 
+// Translation operators of a plan in one basis of singular coordinates.  Set 0
+// takes singular vectors of one reflection class each (tsvd_factors_parity):
+// one M2L operator serves every reflection of its offset and the segmented
+// M2L applies it.  Set 1 takes them as the SVD leaves them, with one M2L
+// operator per offset (or its two factors), for the pairwise M2L.
+struct OpSet {
+  bool built = false;
+  void *pool1 = nullptr;           // swizzled ld x ld matrices
+  int64_t pool1_count = 0, poolbf_count = 0;
+  void *pool_bf = nullptr;         // bf16x3 mode: split M2L operators
+  int bf_kb = 0;                   // 32-wide k blocks per row block in pool_bf
+  // matrix ids (pool1 unless noted) per level; -1 when absent
+  std::vector<int> utu_id, vsu_id, utd_id, vsd_id;  // truncated-SVD factors
+  std::vector<int> rank_u, rank_d;                  // their ranks
+  std::vector<std::vector<int>> m2m_id;             // [parent level][octant]
+  std::vector<std::vector<int>> l2l_id;             // [parent level][octant]
+  std::vector<std::vector<int>> m2l_id;             // [level][343 offset code] (set 0: offsets with no negative
+                                                    // component; factored: the left factor L)
+  std::vector<std::vector<int>> m2l_r_id;           // factored M2L: the right factor R, same indexing
+  std::vector<std::vector<int>> m2l_k;              // factored M2L: rank k per (level, offset)
+  int m2l_ldt = 0;                                  // factored M2L: row length of the per-pair intermediate
+  uint8_t *d_par = nullptr;                         // set 0: sign bytes, [upward, downward][maxlevel + 1][ld]
+  uint32_t *d_tiles = nullptr;                      // set 0: M2LArgs::tiles
+  std::vector<double> vs_alpha;                     // Laplace level scaling
+};
+
 struct PassLists {
   int nr = 0;
   // per level l (index l, levels >= 2), in singular coordinates c = U^T chk
@@ -125,10 +211,13 @@ struct PassLists {
   GemmBatch vs_u;               // c_u -> upward equivalent (M2P sources), all levels
   GemmBatch ut_dx;              // P2L check -> its own c_d array (added by the M2L sums), all levels
   GemmBatch vs_d;               // c_d -> downward equivalent (leaves), all levels
-  GemmBatch m2l;                // all levels, c_u -> pair slots of c_d (factored: intermediate -> slots)
+  M2LBatch m2lc;                // segmented M2L: all levels, c_u -> column slots of c_d
+  GemmBatch m2l;                // pairwise M2L: c_u -> pair slots (factored: per-pair intermediate -> slots)
   GemmBatch m2l_r;              // factored M2L: c_u -> per-pair intermediate (R factors)
-  std::vector<int> m2l_t0;      // per level (0 .. maxlevel + 1): the first M2L task of that level (tasks
-                                // ascend by level; entry maxlevel + 1 = the task count)
+  // per level (0 .. maxlevel + 1): the first task of that level in m2l (tasks
+  // ascend by level; entry maxlevel + 1 = the task count)
+  std::vector<int> m2l_t0;
+  int32_t *d_m2l_rows = nullptr;  // per box: rows of its M2L sums (its level's downward rank, to 16)
 };
 
 struct DevTree {
@@ -158,10 +247,10 @@ struct DevTree {
   void *x_o = nullptr;          // T4 per X entry: source leaf centre - target box centre
   int nxbox = 0;
   int32_t *v_tgt = nullptr;     // boxes at level >= 2 (M2L sums)
-  int32_t *v_off = nullptr;     // pair ids of each such box (CSR)
+  int32_t *v_off = nullptr;     // M2L columns of each such box (CSR)
   int32_t *v_pair = nullptr;
   int nvbox = 0;
-  int64_t nvpair = 0;
+  int64_t nvcol = 0;
   // per level: non-leaf boxes, CSR of their children (for the M2M sums)
   std::vector<int32_t *> m2m_tgt, m2m_off, m2m_kid;
   std::vector<int> m2m_n;
@@ -196,40 +285,33 @@ struct fmm_plan {
   std::vector<int64_t> loff[4];      // U, V, W, X CSR offsets (nbox+1)
   std::vector<int64_t> lidx[4];
   std::vector<int32_t> leaf_ids;
-  std::vector<int32_t> vpair_src, vpair_tgt;  // V pairs in GEMM order
+  std::vector<int32_t> vpair_src, vpair_pos;  // pairwise M2L: V pairs in GEMM order (sort_pairs)
+  std::vector<int64_t> vpair_first;
+  // M2L columns in GEMM order: eight source boxes (-1: absent), level * 27 +
+  // shape, reflection
+  std::vector<int32_t> mcol_src, mcol_key;
+  std::vector<uint8_t> mcol_flip;
   std::vector<int32_t> p2l_boxes;             // boxes whose X list goes through P2L
   int64_t p2p_inter = 0, far_inter = 0;
   std::vector<int64_t> item_pairs;  // pair interactions (targets x near sources) per leaf item, in launch order
   // device
   fmm::DevTree dt;
   void *surf = nullptr;            // T4 grid offsets in [-1,1]^3, nsurf entries
-  void *pool1 = nullptr;           // swizzled ld x ld matrices
-  int64_t pool1_count = 0, poolbf_count = 0;
-  void *pool_bf = nullptr;         // bf16x3 mode: split M2L operators
-  int bf_kb = 0;                   // 32-wide k blocks per row block in pool_bf
-  // matrix ids (pool1 unless noted) per level; -1 when absent
-  std::vector<int> utu_id, vsu_id, utd_id, vsd_id;  // truncated-SVD factors
-  std::vector<int> rank_u, rank_d;                  // their ranks
-  std::vector<std::vector<int>> m2m_id;             // [parent level][octant]
-  std::vector<std::vector<int>> l2l_id;             // [parent level][octant]
-  std::vector<std::vector<int>> m2l_id;             // [level][343 offset code] (factored: the left factor L)
-  std::vector<std::vector<int>> m2l_r_id;           // factored M2L: the right factor R, same indexing
-  std::vector<std::vector<int>> m2l_k;              // factored M2L: rank k per (level, offset)
-  int m2l_ldt = 0;                                  // factored M2L: row length of the per-pair intermediate
-  std::vector<double> vs_alpha, k_alpha;            // Laplace level scaling
+  fmm::OpSet ops[2];               // translation operators (OpSet)
   // work arrays, sized for work_nr columns
-  int work_nr = 0;
+  int work_nr = 0, colbuf_nr = 0, pairbuf_nr = 0;
   void *qs = nullptr, *equ = nullptr, *chk = nullptr, *eqd = nullptr, *chku = nullptr,
-       *cu = nullptr, *yd = nullptr, *pairbuf = nullptr, *mslot = nullptr, *ydx = nullptr, *m2l_t = nullptr;
+       *cu = nullptr, *yd = nullptr, *pairbuf = nullptr, *colbuf = nullptr, *cub = nullptr, *mslot = nullptr, *ydx = nullptr, *m2l_t = nullptr;
+  // cub: cu split into bf16 high and low parts (bf16x3, segmented M2L)
   // cu: upward check in singular coordinates (U_u^T chk); yd: downward
   // check in singular coordinates (M2L sums + U_d^T chk)
-  fmm::PassLists lists_by_nr[fmm::MAX_NR + 1];  // task lists per column count
+  fmm::PassLists lists[2][fmm::MAX_NR + 1];  // task lists per operator set and column count
   // P2M targets (leaves at level >= 2) and per-leaf flags
   int p2m_count = 0;
   int32_t *d_p2m_box = nullptr;   // box ids
   int32_t *d_p2m_off = nullptr;   // 0..p2m_count (each box is its own source)
   int32_t *d_has_local = nullptr; // per leaf slot: level >= 2
-  int32_t *d_m2l_rows = nullptr;  // per box: rows of its M2L sums (its level's downward rank, to 16)
+  int32_t *d_vp_off = nullptr, *d_vp_pair = nullptr;  // pairwise M2L: pair slots of each box at level >= 2
   // profiling: event pairs per phase, recorded during fmm_eval
   int profiling = 0;               // bit k set: time phase k
   std::vector<std::pair<int, std::pair<hipEvent_t, hipEvent_t>>> prof_events;
@@ -246,7 +328,7 @@ struct fmm_plan {
   // chained launches of a pair evaluation led by this plan: the M2M levels
   // and the L2L levels of both plans, each in one launch; counters (ticket,
   // finished tasks per phase, error flag) cleared before each launch
-  fmm::Chain chain_up, chain_down;
+  fmm::Chain chain_up[2], chain_down[2];  // [monopole + dipole sources]
   int32_t *chain_ctr = nullptr;
   int chain_ctr_n = 0;
   uint64_t coord_hash = 0;          // checksum of the FP64 input coordinates (per molecule, chained)
@@ -264,3 +346,12 @@ struct fmm_plan {
   int ops_shared = 0;
   std::vector<void *> *alloc_sink = nullptr;    // where dev_alloc records a buffer (null: allocs)
 };
+
+namespace fmm {
+inline int op_set(const fmm_plan *P, bool keeps_order) {
+  return P->tune.m2l_factored ||
+                 (P->precision != FMM_FP64 && (keeps_order || P->dt.nvcol < M2L_FEW_COLUMNS))
+             ? 1
+             : 0;
+}
+}  // namespace fmm

@@ -628,12 +628,13 @@ __device__ inline unsigned short f2bf_rne(float x) {
 }
 __device__ inline float bf2f(unsigned short h) { return __uint_as_float((unsigned int)h << 16); }
 
-template <int RBW, int NT = GEMM_NT>
+template <int RBW>
 __global__ __launch_bounds__(256) void k_gemm_bf3(GemmArgs g0, GemmArgs g1, int KB) {
   __builtin_amdgcn_s_setprio(3);
   GemmArgs g;
   int task;
   if (!gemm_pick(g0, g1, g, task)) return;
+  constexpr int NT = GEMM_NT;
   const GemmTask tk = g.tasks[task];
   const int ld = g.ldx, ldy = g.ldy, mode = g.mode;
   const int nrb = tk.nrb > 0 ? min(tk.nrb, g.nrb) : g.nrb;
@@ -735,6 +736,384 @@ __global__ __launch_bounds__(256) void k_gemm_bf3(GemmArgs g0, GemmArgs g1, int 
       }
     }
   }
+}
+
+// ---------------------------------------------------------------------------
+// Segmented M2L (M2LTask): one workgroup of NW waves sums up to eight operator
+// products into one column block, so a target's children of one source
+// parent meet in the accumulators instead of in per-pair slots in memory.
+// What bounds it: MFMA issue in FP32 and FP64 and operator traffic from L2 in
+// bf16x3; the former form (one 64-column task per (level, offset), a slot per
+// V pair) was bound by those slots' way through memory and by task fill.
+// Layout: wave w takes row blocks w, w + NW, ... of every column block, so its
+// operator fragments come straight from memory (coalesced, one step ahead)
+// and the columns, which every wave reads, go through LDS in 64-wide k chunks,
+// double buffered with the next chunk's gather in flight; one barrier per
+// chunk.  The k loop runs over the concatenated segments; a (segment, column
+// block) with no source is skipped.
+// ---------------------------------------------------------------------------
+// Workgroup -> (plan, task).  Workgroup b runs on XCD b % 8; runs of M2L_RUN
+// consecutive tasks (one shape, the same operators) go to one XCD's L2, and
+// the runs are dealt over the XCDs, since tasks differ in their segments.
+constexpr int M2L_RUN = 4;
+__host__ __device__ inline int m2l_grid(int ntask) { return (ntask + 8 * M2L_RUN - 1) / (8 * M2L_RUN) * 8 * M2L_RUN; }
+__device__ inline bool m2l_pick(const M2LArgs &g0, const M2LArgs &g1, M2LArgs &g, int &task) {
+  const int n0 = m2l_grid(g0.ntask);
+  int b = (int)blockIdx.x;
+  const bool second = b >= n0;
+  g = second ? g1 : g0;
+  if (second) b -= n0;
+  const int i = b >> 3;
+  task = (i / M2L_RUN * 8 + (b & 7)) * M2L_RUN + i % M2L_RUN;
+  return task < g.ntask;
+}
+
+// The task's tables in LDS.  s_src: source rows, segment by segment, then one
+// more segment of the zero row (k past the end reads it); s_flip: column
+// reflections; s_sign: per reflection m and coordinate k the sign bits to
+// flip, laid out like the values (HALF: two bf16 to a word, else one word per
+// value: its high word in FP64).
+template <int NT, int NTHR, bool HALF>
+__device__ __forceinline__ void m2l_tables(const M2LArgs &g, const M2LTask *__restrict__ tk, int32_t *s_src,
+                                           uint8_t *s_flip, uint32_t *s_sign) {
+  const int tid = (int)threadIdx.x, nseg = tk->nseg, ncol = tk->ncol, klen = tk->klen;
+  const uint8_t *__restrict__ par = g.par_u + (int64_t)tk->tab * g.ldx;
+  const int32_t *__restrict__ src = g.src + tk->src0;
+  for (int i = tid; i < (nseg + 1) * NT; i += NTHR) {
+    const int r = i < nseg * NT ? src[i] : -1;
+    s_src[i] = r < 0 ? g.zrow : r;
+  }
+  for (int i = tid; i < NT; i += NTHR) s_flip[i] = i < ncol ? g.flip[tk->col0 + i] : 0;
+  const int words = HALF ? klen >> 1 : klen;
+  for (int i = tid; i < words; i += NTHR) {
+    const uint32_t w0 = HALF ? (2 * i < g.ldx ? par[2 * i] : 0u) : (i < g.ldx ? par[i] : 0u);
+    const uint32_t w1 = HALF && 2 * i + 1 < g.ldx ? par[2 * i + 1] : 0u;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const uint32_t a = (w0 >> m) & 1u, b = (w1 >> m) & 1u;
+      s_sign[m * words + i] = HALF ? (a << 15) | (b << 31) : a << 31;
+    }
+  }
+}
+
+// This thread's share of the gathered columns: of a KC-wide k chunk of NT
+// columns, units of 16 bytes (unit j * NTHR + tid) of NP planes (bf16x3: high
+// and low parts), as loaded, with their sign words.  Every load is issued on
+// every path: loads under a condition would make the compiler wait for all
+// loads in flight.  k past a row's end (klen rounds up to 32) reads the row's
+// last values, which meet zero operator columns.
+template <typename E, int NP, int NT, int NTHR, int KC>
+struct M2LGather {
+  static constexpr int VE = 16 / (int)sizeof(E), UPC = KC / VE, NU = (NT * UPC + NTHR - 1) / NTHR;
+  static constexpr int SW = sizeof(E) == 8 ? 2 : 4;  // sign words per unit
+  typedef E VT __attribute__((ext_vector_type(VE)));
+  typedef uint32_t SG __attribute__((ext_vector_type(SW)));
+  uint4 v[NU][NP];
+  SG sg[NU];
+
+  __device__ __forceinline__ static int unit(int j) {
+    const int u = j * NTHR + (int)threadIdx.x;
+    return NT * UPC % NTHR ? min(u, NT * UPC - 1) : u;  // the last unit by several threads
+  }
+  __device__ __forceinline__ void load(int kc, int klen, uint32_t rcp, int nseg, const E *const (&X)[NP], int ldx,
+                                       const int32_t *__restrict__ s_src, const uint8_t *__restrict__ s_flip,
+                                       const uint32_t *__restrict__ s_sign) {
+    const int words = sizeof(E) == 2 ? klen >> 1 : klen;
+#pragma unroll
+    for (int j = 0; j < NU; ++j) {
+      const int u = unit(j), col = u / UPC, k0 = kc + (u % UPC) * VE;
+      const int sgm = (int)__umulhi((uint32_t)k0, rcp);  // k0 / klen
+      const int kk = k0 - sgm * klen;
+      const int64_t off = (int64_t)s_src[min(sgm, nseg) * NT + col] * ldx + min(kk, ldx - VE);
+#pragma unroll
+      for (int p = 0; p < NP; ++p) v[j][p] = *reinterpret_cast<const uint4 *>(X[p] + off);
+      sg[j] = *reinterpret_cast<const SG *>(s_sign + s_flip[col] * words + (sizeof(E) == 2 ? kk >> 1 : kk));
+    }
+  }
+
+  // store(plane, col, k, values): the units of this thread, signs applied
+  template <typename F>
+  __device__ __forceinline__ void stage(F store) const {
+#pragma unroll
+    for (int j = 0; j < NU; ++j) {
+      const int u = unit(j);
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        uint4 x = v[j][p];
+        if constexpr (SW == 4) {
+          x.x ^= sg[j][0]; x.y ^= sg[j][1]; x.z ^= sg[j][2]; x.w ^= sg[j][3];
+        } else {
+          x.y ^= sg[j][0]; x.w ^= sg[j][1];
+        }
+        store(p, u / UPC, (u % UPC) * VE, x);
+      }
+    }
+  }
+};
+
+// Signs and store of one accumulator block (rows i0 .. i0 + 3 of column c).
+__device__ inline float flip_sign(float x, uint32_t t, int e) {
+  return __uint_as_float(__float_as_uint(x) ^ ((t << (31 - 8 * e)) & 0x80000000u));
+}
+__device__ inline double flip_sign(double x, uint32_t t, int e) {
+  uint64_t u = (uint64_t)__double_as_longlong(x);
+  u ^= (uint64_t)((t << (31 - 8 * e)) & 0x80000000u) << 32;
+  return __longlong_as_double((long long)u);
+}
+template <typename V4, typename T>
+__device__ __forceinline__ void m2l_store(V4 v, const uint8_t *__restrict__ par_d, int i0, int flip, T *y) {
+  const uint32_t t = (*reinterpret_cast<const uint32_t *>(par_d + i0) >> flip) & 0x01010101u;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = flip_sign(v[e], t, e);
+  *reinterpret_cast<V4 *>(y + i0) = v;
+}
+
+template <typename T, int NW, int RBW, int NC, int KC, int WPE>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) void k_m2l(M2LArgs g0, M2LArgs g1) {
+  __builtin_amdgcn_s_setprio(3);
+  using V4 = typename Vec4<T>::type;
+  constexpr int NT = 16 * NC, NTHR = 64 * NW, PITCH = KC + 16 / (int)sizeof(T), AQ = KC / 16;
+  using Gather = M2LGather<T, 1, NT, NTHR, KC>;
+  typedef typename Gather::VT VT;
+  M2LArgs g;
+  int task;
+  if (!m2l_pick(g0, g1, g, task)) return;
+  const M2LTask *__restrict__ tk = g.tasks + task;
+  const int rb0 = (int)blockIdx.y * g.rbg, rb1 = min(tk->nrb, rb0 + g.rbg);
+  if (rb0 >= rb1) return;
+  const int nseg = tk->nseg, klen = tk->klen, ncol = tk->ncol;
+  const uint64_t blocks = tk->blocks;
+  extern __shared__ __align__(16) char smem[];
+  T(*Bs)[NT][PITCH] = reinterpret_cast<T(*)[NT][PITCH]>(smem);
+  uint32_t *s_sign = reinterpret_cast<uint32_t *>(smem + 2 * sizeof(T) * NT * PITCH);
+  __shared__ int32_t s_src[9 * NT];
+  __shared__ uint8_t s_flip[NT];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int gi = lane >> 4, ln = lane & 15;
+  const T *const X[1] = {(const T *)g.X};
+  const uint32_t rcp = (uint32_t)(0x100000000ull / (uint32_t)klen) + 1u;
+  const int kend = nseg * klen, Q = klen >> 4;
+  // lane s holds segment s's operator and, per row block of this wave, its
+  // nonzero k groups (none past the last row block), read by readlane
+  const int sl = min(lane, nseg - 1);
+  const int matv = tk->mat[sl];
+  uint32_t mskv[RBW];
+  int64_t roff[RBW];
+#pragma unroll
+  for (int r = 0; r < RBW; ++r) {
+    const int rb = rb0 + wave + r * NW;
+    mskv[r] = rb < rb1 ? g.tiles[((int64_t)tk->tab * 8 + tk->zero[sl]) * (g.ldx >> 4) + rb] : 0u;
+    roff[r] = (int64_t)min(rb, rb1 - 1) * g.kstride * 256;
+  }
+  // operator fragments of this wave's row blocks, k group after k group, a
+  // whole chunk ahead, so that they are older than the gather loads of the
+  // chunk after it (memory counters retire in order: waiting for operators
+  // issued after a gather would wait for the gather)
+  int aseg = 0, akq = 0;
+  auto mat_ptr = [&](int sgm) {
+    return (const T *)g.pool + (int64_t)__builtin_amdgcn_readlane(matv, min(sgm, nseg - 1)) * g.mstride +
+           (int64_t)lane * 4;
+  };
+  const T *__restrict__ A = mat_ptr(0);
+  auto load_a = [&](V4 (&a)[RBW]) {
+#pragma unroll
+    for (int r = 0; r < RBW; ++r) a[r] = *reinterpret_cast<const V4 *>(A + roff[r]);
+    A += 256;
+    if (++akq == Q) {
+      akq = 0;
+      A = mat_ptr(++aseg);
+    }
+  };
+  V4 acc[RBW][NC];
+#pragma unroll
+  for (int r = 0; r < RBW; ++r)
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) acc[r][cb] = V4{0, 0, 0, 0};
+  V4 an[AQ][RBW];
+#pragma unroll
+  for (int q = 0; q < AQ; ++q) load_a(an[q]);
+  m2l_tables<NT, NTHR, false>(g, tk, s_src, s_flip, s_sign);
+  __syncthreads();
+  Gather gt;
+  auto stage = [&](int buf) {
+    gt.stage([&](int, int col, int k, uint4 x) { *reinterpret_cast<uint4 *>(&Bs[buf][col][k]) = x; });
+  };
+  gt.load(0, klen, rcp, nseg, X, g.ldx, s_src, s_flip, s_sign);
+  stage(0);
+  gt.load(KC, klen, rcp, nseg, X, g.ldx, s_src, s_flip, s_sign);
+  __syncthreads();
+  int bseg = 0, bkq = 0;
+  uint32_t have = (uint32_t)blocks, mb[RBW];
+#pragma unroll
+  for (int r = 0; r < RBW; ++r) mb[r] = __builtin_amdgcn_readlane(mskv[r], 0);
+  for (int kc = 0, buf = 0; kc < kend; kc += KC, buf ^= 1) {
+#pragma unroll
+    for (int q = 0; q < KC / 16; ++q) {
+      VT b[NC][4 / Gather::VE];
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb)
+#pragma unroll
+        for (int h = 0; h < 4 / Gather::VE; ++h)
+          b[cb][h] = *reinterpret_cast<const VT *>(&Bs[buf][cb * 16 + ln][q * 16 + 4 * gi + h * Gather::VE]);
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb) {
+        if (!((have >> cb) & 1)) continue;
+#pragma unroll
+        for (int r = 0; r < RBW; ++r)
+          if ((mb[r] >> bkq) & 1) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+              acc[r][cb] = mfma_16x16x4(an[q][r][t], b[cb][t / Gather::VE][t % Gather::VE], acc[r][cb]);
+          }
+      }
+      load_a(an[q]);
+      if (++bkq == Q) {
+        bkq = 0;
+        ++bseg;
+        have = bseg < nseg ? (uint32_t)(blocks >> (8 * bseg)) : 0u;
+#pragma unroll
+        for (int r = 0; r < RBW; ++r) mb[r] = __builtin_amdgcn_readlane(mskv[r], min(bseg, nseg - 1));
+      }
+    }
+    stage(buf ^ 1);
+    gt.load(kc + 2 * KC, klen, rcp, nseg, X, g.ldx, s_src, s_flip, s_sign);
+    __syncthreads();
+  }
+  const uint8_t *__restrict__ par_d = g.par_d + (int64_t)tk->tab * g.ldx;
+#pragma unroll
+  for (int cb = 0; cb < NC; ++cb) {
+    const int c = cb * 16 + ln;
+    if (c >= ncol) continue;
+    T *__restrict__ y = (T *)g.Y + (int64_t)(tk->col0 + c) * g.ldy;
+#pragma unroll
+    for (int r = 0; r < RBW; ++r) {
+      const int rb = rb0 + wave + r * NW;
+      if (rb < rb1) m2l_store(acc[r][cb], par_d, rb * 16 + 4 * gi, s_flip[c], y);
+    }
+  }
+}
+
+// The same in bf16x3 (operands split into bf16 high and low parts, three
+// products, FP32 accumulation, as in k_gemm_bf3), on columns that k_split_bf3
+// has split once: split in every gather, the VALU work of staging outweighed
+// the MFMA work.  klen is a multiple of 32.  MFMA issue does not bound this
+// form, so absent sources and zero tiles are multiplied like the rest and the
+// loop has no branches on them; a row block past the last one repeats it.
+template <int NW, int RBW, int NC, int KC, int WPE>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) void k_m2l_bf3(M2LArgs g0, M2LArgs g1) {
+  __builtin_amdgcn_s_setprio(3);
+  constexpr int NT = 16 * NC, NTHR = 64 * NW, PITCH = KC + 8, AQ = KC / 32;
+  using Gather = M2LGather<unsigned short, 2, NT, NTHR, KC>;
+  M2LArgs g;
+  int task;
+  if (!m2l_pick(g0, g1, g, task)) return;
+  const M2LTask *__restrict__ tk = g.tasks + task;
+  const int rb0 = (int)blockIdx.y * g.rbg, rb1 = min(tk->nrb, rb0 + g.rbg);
+  if (rb0 >= rb1) return;
+  const int nseg = tk->nseg, klen = tk->klen, ncol = tk->ncol;
+  extern __shared__ __align__(16) char smem[];
+  // [buffer][plane][column][k]
+  unsigned short(*Bs)[2][NT][PITCH] = reinterpret_cast<unsigned short(*)[2][NT][PITCH]>(smem);
+  uint32_t *s_sign = reinterpret_cast<uint32_t *>(smem + 4 * sizeof(unsigned short) * NT * PITCH);
+  __shared__ int32_t s_src[9 * NT];
+  __shared__ uint8_t s_flip[NT];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int gi = lane >> 4, ln = lane & 15;
+  const unsigned short *const X[2] = {(const unsigned short *)g.X, (const unsigned short *)g.X + g.xlo};
+  const uint32_t rcp = (uint32_t)(0x100000000ull / (uint32_t)klen) + 1u;
+  const int kend = nseg * klen, Q = klen >> 5;
+  const int matv = tk->mat[min(lane, nseg - 1)];
+  int aseg = 0, akb = 0;
+  auto mat_ptr = [&](int sgm) {
+    return (const uint4 *)g.pool + (int64_t)__builtin_amdgcn_readlane(matv, min(sgm, nseg - 1)) * g.mstride + lane;
+  };
+  const uint4 *__restrict__ A = mat_ptr(0);
+  int64_t roff[RBW];
+#pragma unroll
+  for (int r = 0; r < RBW; ++r) roff[r] = (int64_t)min(rb0 + wave + r * NW, rb1 - 1) * g.kstride * 128;
+  auto load_a = [&](uint4 (&a)[RBW][2]) {
+#pragma unroll
+    for (int r = 0; r < RBW; ++r) {
+      a[r][0] = A[roff[r]];
+      a[r][1] = A[roff[r] + 64];
+    }
+    A += 128;
+    if (++akb == Q) {
+      akb = 0;
+      A = mat_ptr(++aseg);
+    }
+  };
+  floatx4 acc[RBW][NC];
+#pragma unroll
+  for (int r = 0; r < RBW; ++r)
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) acc[r][cb] = floatx4{0, 0, 0, 0};
+  uint4 an[AQ][RBW][2];
+#pragma unroll
+  for (int q = 0; q < AQ; ++q) load_a(an[q]);
+  m2l_tables<NT, NTHR, true>(g, tk, s_src, s_flip, s_sign);
+  __syncthreads();
+  Gather gt;
+  auto stage = [&](int buf) {
+    gt.stage([&](int p, int col, int k, uint4 x) { *reinterpret_cast<uint4 *>(&Bs[buf][p][col][k]) = x; });
+  };
+  gt.load(0, klen, rcp, nseg, X, g.ldx, s_src, s_flip, s_sign);
+  stage(0);
+  gt.load(KC, klen, rcp, nseg, X, g.ldx, s_src, s_flip, s_sign);
+  __syncthreads();
+  for (int kc = 0, buf = 0; kc < kend; kc += KC, buf ^= 1) {
+#pragma unroll
+    for (int q = 0; q < KC / 32; ++q) {
+      bf16x8 b[2][NC];
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb)
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+          b[p][cb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8 *>(&Bs[buf][p][cb * 16 + ln][q * 32 + 8 * gi]));
+#pragma unroll
+      for (int pr = 0; pr < 3; ++pr)  // hi*hi, hi*lo, lo*hi
+#pragma unroll
+        for (int cb = 0; cb < NC; ++cb)
+#pragma unroll
+          for (int r = 0; r < RBW; ++r)
+            acc[r][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, an[q][r][pr == 2]),
+                                                                 b[pr == 1][cb], acc[r][cb], 0, 0, 0);
+      load_a(an[q]);
+    }
+    stage(buf ^ 1);
+    gt.load(kc + 2 * KC, klen, rcp, nseg, X, g.ldx, s_src, s_flip, s_sign);
+    __syncthreads();
+  }
+  const uint8_t *__restrict__ par_d = g.par_d + (int64_t)tk->tab * g.ldx;
+#pragma unroll
+  for (int cb = 0; cb < NC; ++cb) {
+    const int c = cb * 16 + ln;
+    if (c >= ncol) continue;
+    float *__restrict__ y = (float *)g.Y + (int64_t)(tk->col0 + c) * g.ldy;
+#pragma unroll
+    for (int r = 0; r < RBW; ++r) {
+      const int rb = rb0 + wave + r * NW;
+      if (rb < rb1) m2l_store(acc[r][cb], par_d, rb * 16 + 4 * gi, s_flip[c], y);
+    }
+  }
+}
+
+// Upward coordinates split into bf16 high and low parts (x = hi + lo), rows
+// [row0, row1) of row length ld; blockIdx.y = 1: a second plan's.
+__global__ __launch_bounds__(256) void k_split_bf3(const float *__restrict__ x0, unsigned short *__restrict__ y0,
+                                                   const float *__restrict__ x1, unsigned short *__restrict__ y1,
+                                                   int64_t first, int64_t count, int64_t lo) {
+  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  const int64_t i = 4 * (blockIdx.x * 256ll + threadIdx.x);
+  if (i >= count) return;
+  const float *__restrict__ x = (blockIdx.y ? x1 : x0) + first;
+  unsigned short *__restrict__ y = (blockIdx.y ? y1 : y0) + first;
+  const floatx4 v = *reinterpret_cast<const floatx4 *>(x + i);
+  const bf16x4 h = __builtin_convertvector(v, bf16x4);
+  *reinterpret_cast<bf16x4 *>(y + i) = h;
+  *reinterpret_cast<bf16x4 *>(y + lo + i) = __builtin_convertvector(v - __builtin_convertvector(h, floatx4), bf16x4);
 }
 
 // ---------------------------------------------------------------------------
@@ -1799,12 +2178,12 @@ static GemmArgs gemm_args(const fmm_plan *P, const GemmBatch &bt, const void *X,
   g.seg = bt.seg ? bt.seg : P->ld;
   g.KQ = bt.kq_stride ? bt.kq_stride : P->ld / 16;
   g.mode = bt.mode;
-  g.nt = bt.nt;
+  const OpSet &O = P->ops[bt.set];
   if (bt.pool == 2) {
-    g.pool = P->pool_bf;
-    g.mstride = (int64_t)(P->ld / 16) * P->bf_kb * 2 * 64;
+    g.pool = O.pool_bf;
+    g.mstride = (int64_t)(P->ld / 16) * O.bf_kb * 2 * 64;
   } else {
-    g.pool = P->pool1;
+    g.pool = O.pool1;
     g.mstride = (int64_t)P->ld * P->ld;
   }
   return g;
@@ -1817,10 +2196,7 @@ static void launch_gemm_rbw(const GemmArgs &g0, const GemmArgs &g1, bool bf3, in
   const unsigned gx = 8u * (unsigned)((g0.ntask + 7) / 8 + (g1.ntask + 7) / 8);
   if constexpr (std::is_same<T, float>::value) {
     if (bf3) {
-      if (g0.nt == 2 * GEMM_NT)
-        hipLaunchKernelGGL((k_gemm_bf3<RBW, 2 * GEMM_NT>), dim3(gx, gy), dim3(256), 0, s, g0, g1, KB);
-      else
-        hipLaunchKernelGGL((k_gemm_bf3<RBW>), dim3(gx, gy), dim3(256), 0, s, g0, g1, KB);
+      hipLaunchKernelGGL((k_gemm_bf3<RBW>), dim3(gx, gy), dim3(256), 0, s, g0, g1, KB);
       return;
     }
   }
@@ -1882,7 +2258,7 @@ static int launch_gemm2(fmm_plan *P, const GemmBatch &bt, const T *X, T *Y, fmm_
   // Mpoints/s, 1 -> 47.0.  Single precision keeps one group of up to 8
   // (two blocks per wave cost 3% there).
   if (std::is_same<T, double>::value) rbw = std::min(rbw, 2);
-  const int KB = P->bf_kb;
+  const int KB = P->ops[bt.set].bf_kb;
   switch (rbw) {
     case 1: launch_gemm_rbw<T, 1>(g0, g1, bf3, KB, s); break;
     case 2: launch_gemm_rbw<T, 2>(g0, g1, bf3, KB, s); break;
@@ -1925,8 +2301,176 @@ static int launch_gemm(fmm_plan *P, const GemmBatch &bt, const T *X, T *Y, hipSt
   return launch_gemm2<T>(P, bt, X, Y, nullptr, nullptr, nullptr, nullptr, s);
 }
 
-int ensure_lists(fmm_plan *P, int nr);   // host planner
+int ensure_lists(fmm_plan *P, int nr, int set);   // host planner
+int ensure_m2l(fmm_plan *P, int nr, int set);
 int ensure_work(fmm_plan *P, int nr);
+
+// Segmented M2L of the levels [l0, l1) of plan P and, when Q is given, of plan Q
+// (sharing P's tree and precision), one launch.
+template <typename T>
+static int launch_m2l(fmm_plan *P, fmm_plan *Q, int nr, int l0, int l1, hipStream_t s) {
+  auto args = [&](fmm_plan *F) {
+    const PassLists &L = F->lists[0][nr];
+    const OpSet &O = F->ops[0];
+    const bool bf3 = F->precision == FMM_FP32_BF16X3;
+    M2LArgs g;
+    // l0 and l1 are 0, the second finest level or past the finest one
+    const int t0 = l0 ? L.m2lc.split : 0, t1 = l1 <= F->dt.maxlevel ? L.m2lc.split : L.m2lc.ntask;
+    g.tasks = L.m2lc.d_tasks + t0;
+    g.ntask = t1 - t0;
+    g.src = L.m2lc.d_src;
+    g.flip = L.m2lc.d_flip;
+    g.par_u = O.d_par;
+    g.par_d = O.d_par + (size_t)(F->dt.maxlevel + 1) * F->ld;
+    g.tiles = O.d_tiles;
+    g.pool = bf3 ? O.pool_bf : O.pool1;
+    g.mstride = bf3 ? (int64_t)(F->ld / 16) * O.bf_kb * 2 * 64 : (int64_t)F->ld * F->ld;
+    g.X = bf3 ? F->cub : F->cu;
+    // the row past the buffer's last box is never written
+    g.zrow = F->dt.nbox * (bf3 ? F->colbuf_nr : F->work_nr);
+    g.xlo = ((int64_t)g.zrow + 1) * F->ld;
+    g.Y = F->colbuf;
+    g.nrb = L.m2lc.nrb;
+    g.nrbk = L.m2lc.nrbk;
+    g.ldx = F->ld;
+    g.ldy = L.m2lc.ldy;
+    g.kstride = bf3 ? O.bf_kb : F->ld / 16;
+    return g;
+  };
+  M2LArgs g0 = args(P), g1 = g0;
+  g1.ntask = 0;
+  if (Q) g1 = args(Q);
+  if (g0.ntask == 0) { std::swap(g0, g1); g1.ntask = 0; }
+  if (g0.ntask == 0) return FMM_OK;
+  const int nrb = std::max(g0.nrb, g1.ntask ? g1.nrb : 0);
+  const int nt = P->lists[0][nr].m2lc.nt;
+  const unsigned gx = (unsigned)(m2l_grid(g0.ntask) + m2l_grid(g1.ntask));
+  // Waves of a workgroup, two row blocks each (few registers, so that a SIMD
+  // holds four and more waves to hide the operator loads): as many as the rank
+  // needs up to 6 in single precision; 3 in double, whose larger ranks, like
+  // single precision's from 13 row blocks and a lower gemm_rbw, split the
+  // rows over the grid.
+  if (P->precision == FMM_FP32_BF16X3) {
+    // the boxes of the levels [l0, l1); a row past the last box stays zero
+    const int64_t first = P->level_begin[std::min<int>(l0, P->dt.maxlevel + 1)] * nr * P->ld;
+    const int64_t count = P->level_begin[l1] * nr * P->ld - first;
+    if (count > 0)
+      hipLaunchKernelGGL(k_split_bf3, dim3((unsigned)((count / 4 + 255) / 256), Q ? 2 : 1), dim3(256), 0, s,
+                         (const float *)P->cu, (unsigned short *)P->cub, Q ? (const float *)Q->cu : nullptr,
+                         Q ? (unsigned short *)Q->cub : nullptr, first, count, g0.xlo);
+    FMM_HIP_TRY(hipGetLastError());
+  }
+  // Waves x row blocks per wave, columns and k chunk of a workgroup.  Single
+  // precision: 4 x 3 row blocks of 64 columns, 32 k at a time, fits four waves
+  // to a SIMD (128 registers); against it, FP32 / bf16x3 at 1M / 0.8M columns:
+  // 336 / 212 us, 64 k at a time 337 / 230, 32 columns 362 / 244, 6 waves x 2
+  // 489 / 298, 3 waves x 3 398 / 296 us.  Ranks up to 8 row blocks take 4 x 2.
+  // Double: 4 x 2 of 32 columns, 64 k at a time: 736 us, 32 k 754, 64 columns
+  // 842, 8 waves x 2 791 us.  More row blocks (and a smaller gemm_rbw) are
+  // split over the grid.
+  auto go = [&](auto r, auto c, auto kc, auto wpe) {
+    constexpr int RBW = decltype(r)::value, NC = decltype(c)::value, KC = decltype(kc)::value,
+                  WPE = decltype(wpe)::value;
+    const int cap = 4 * (P->tune.gemm_rbw > 0 ? std::min(RBW, P->tune.gemm_rbw) : RBW);
+    const int gy = (nrb + cap - 1) / cap;
+    g0.rbg = g1.rbg = (nrb + gy - 1) / gy;
+    const dim3 grid(gx, (unsigned)gy), wg(256);
+    const int nrbk = std::max(g0.nrbk, g1.ntask ? g1.nrbk : 0);
+    if constexpr (std::is_same<T, float>::value) {
+      if (P->precision == FMM_FP32_BF16X3) {
+        const size_t lds = 4 * 2 * 16 * NC * (KC + 8) + 8 * 4 * 16 * ((nrbk + 1) / 2);
+        hipLaunchKernelGGL((k_m2l_bf3<4, RBW, NC, KC, WPE>), grid, wg, lds, s, g0, g1);
+        return;
+      }
+    }
+    if constexpr (NC <= 4) {
+      const size_t lds = 2 * 16 * NC * (KC * sizeof(T) + 16) + 8 * 4 * 16 * nrbk;
+      hipLaunchKernelGGL((k_m2l<T, 4, RBW, NC, KC, WPE>), grid, wg, lds, s, g0, g1);
+    }
+  };
+  typedef std::integral_constant<int, 1> I1;
+  typedef std::integral_constant<int, 2> I2;
+  typedef std::integral_constant<int, 3> I3;
+  typedef std::integral_constant<int, 4> I4;
+  typedef std::integral_constant<int, 8> I8;
+  typedef std::integral_constant<int, 32> I32;
+  typedef std::integral_constant<int, 64> I64;
+  if constexpr (std::is_same<T, double>::value) {
+    if (nt == 16) go(I2(), I1(), I64(), I3());
+    else go(I2(), I2(), I64(), I3());
+  } else {
+    if (nt == 16 && nrb <= 8) go(I2(), I1(), I32(), I4());
+    else if (nt == 16) go(I3(), I1(), I32(), I4());
+    else if (nt == 2 * GEMM_NT) go(I3(), I8(), I32(), I2());
+    else if (nrb <= 8) go(I2(), I4(), I32(), I4());
+    else go(I3(), I4(), I32(), I4());
+  }
+  FMM_HIP_TRY(hipGetLastError());
+  return FMM_OK;
+}
+
+// M2L of plan P and, when Q is given, of plan Q (sharing P's tree and
+// precision), levels [l0, l1): one launch for the plans of one form (a
+// factored plan first maps its upward coordinates through R).
+template <typename T>
+static int launch_m2l_form(fmm_plan *P, fmm_plan *Q, int nr, bool keeps_order, int l0, int l1, hipStream_t s) {
+  const bool pp = op_set(P, keeps_order) == 1, pq = Q && op_set(Q, keeps_order) == 1;
+  int rc;
+  if (!pp || (Q && !pq)) {
+    if ((rc = launch_m2l<T>(pp ? Q : P, !pp && Q && !pq ? Q : nullptr, nr, l0, l1, s))) return rc;
+  }
+  auto pair_gemm = [&](fmm_plan *A, fmm_plan *B) -> int {
+    auto levels = [&](fmm_plan *F) {
+      const PassLists &L = F->lists[1][nr];
+      GemmBatch b = L.m2l;
+      b.d_tasks += L.m2l_t0[l0];
+      b.ntask = L.m2l_t0[l1] - L.m2l_t0[l0];
+      return b;
+    };
+    // factored (l0 .. l1 then spans every level): A and B both or A alone
+    const bool f = A->tune.m2l_factored != 0;
+    const GemmBatch ba = levels(A), bb = B ? levels(B) : GemmBatch();
+    if (f) {
+      const GemmBatch &ra = A->lists[1][nr].m2l_r, &rb = B ? B->lists[1][nr].m2l_r : ra;
+      int r = launch_gemm2<T>(A, ra, (const T *)A->cu, (T *)A->m2l_t, B, &rb, B ? (const T *)B->cu : nullptr,
+                              B ? (T *)B->m2l_t : nullptr, s);
+      if (r) return r;
+    }
+    return launch_gemm2<T>(A, ba, (const T *)(f ? A->m2l_t : A->cu), (T *)A->pairbuf, B, &bb,
+                           B ? (const T *)(f ? B->m2l_t : B->cu) : nullptr, B ? (T *)B->pairbuf : nullptr, s);
+  };
+  if (pp && pq && (P->tune.m2l_factored != 0) == (Q->tune.m2l_factored != 0)) return pair_gemm(P, Q);
+  if (pp && (rc = pair_gemm(P, nullptr))) return rc;
+  if (pq && (rc = pair_gemm(Q, nullptr))) return rc;
+  return FMM_OK;
+}
+
+// The sums of the M2L slots per target box, plus the P2L projections.
+template <typename T>
+static int launch_m2l_sum(fmm_plan *P, fmm_plan *Q, int nr, bool keeps_order, hipStream_t s) {
+  const DevTree &D = P->dt;
+  if (D.nvbox == 0) return FMM_OK;
+  const bool pp = op_set(P, keeps_order) == 1, pq = Q && op_set(Q, keeps_order) == 1;
+  auto go = [&](fmm_plan *A, fmm_plan *B, bool pw) {
+    auto ldp = [&](fmm_plan *F) { return pw ? F->lists[1][nr].m2l.ldy : F->lists[0][nr].m2lc.ldy; };
+    auto rows = [&](fmm_plan *F) { return 16 * (pw ? F->lists[1][nr].m2l.nrb : F->lists[0][nr].m2lc.nrb); };
+    auto slots = [&](fmm_plan *F) { return (const T *)(pw ? F->pairbuf : F->colbuf); };
+    hipLaunchKernelGGL(k_pair_reduce<T>, dim3(D.nvbox, B ? 2 : 1), dim3(64), 0, s, D.v_tgt,
+                       pw ? A->d_vp_off : D.v_off, pw ? A->d_vp_pair : D.v_pair, slots(A), (T *)A->yd, nr, A->ld,
+                       ldp(A), rows(A), B ? slots(B) : nullptr, B ? (T *)B->yd : nullptr, B ? ldp(B) : 0,
+                       B ? rows(B) : 0, (const int32_t *)A->lists[pw][nr].d_m2l_rows,
+                       B ? (const int32_t *)B->lists[pw][nr].d_m2l_rows : nullptr,
+                       (const T *)A->ydx, B ? (const T *)B->ydx : nullptr);
+  };
+  if (!Q || pp == pq) {
+    go(P, Q, pp);
+  } else {
+    go(P, nullptr, pp);
+    go(Q, nullptr, pq);
+  }
+  FMM_HIP_TRY(hipGetLastError());
+  return FMM_OK;
+}
 
 // Densities into Morton order (and, for one column, into the points' fourth
 // slot).
@@ -1949,7 +2493,7 @@ static int eval_passes(fmm_plan *P, hipStream_t s) {
   const DevTree &D = P->dt;
   const int64_t N = P->n;
   const int ld = P->ld;
-  const PassLists &L = P->lists_by_nr[NR];
+  const PassLists &L = P->lists[op_set(P, NR == 1)][NR];
   T *qs = (T *)P->qs, *equ = (T *)P->equ, *chk = (T *)P->chk, *eqd = (T *)P->eqd, *chku = (T *)P->chku,
     *cu = (T *)P->cu, *yd = (T *)P->yd;
   const T kappa = (T)P->kappa;
@@ -1994,24 +2538,14 @@ static int eval_passes(fmm_plan *P, hipStream_t s) {
   ev = prof_begin(P, FMM_PHASE_DC2E, s);
   if ((rc = launch_gemm<T>(P, L.ut_dx, chk, (T *)P->ydx, s))) return rc;
   prof_end(P, FMM_PHASE_DC2E, ev, s);
-  // M2L between singular coordinates into pair slots (rows of the largest
+  // M2L between singular coordinates into slots (rows of the largest
   // downward rank, not of the surface size), then a fixed-order sum per
   // target box (every box at level >= 2)
   ev = prof_begin(P, FMM_PHASE_M2L, s);
-  if (L.m2l_r.ntask) {  // factored: R then L through the per-pair intermediate
-    if ((rc = launch_gemm<T>(P, L.m2l_r, cu, (T *)P->m2l_t, s))) return rc;
-    if ((rc = launch_gemm<T>(P, L.m2l, (const T *)P->m2l_t, (T *)P->pairbuf, s))) return rc;
-  } else if ((rc = launch_gemm<T>(P, L.m2l, cu, (T *)P->pairbuf, s))) {
-    return rc;
-  }
+  if ((rc = launch_m2l_form<T>(P, nullptr, NR, NR == 1, 0, D.maxlevel + 1, s))) return rc;
   prof_end(P, FMM_PHASE_M2L, ev, s);
   ev = prof_begin(P, FMM_PHASE_M2L_SUM, s);
-  if (D.nvbox > 0)
-    hipLaunchKernelGGL(k_pair_reduce<T>, dim3(D.nvbox), dim3(64), 0, s, D.v_tgt, D.v_off, D.v_pair,
-                       (const T *)P->pairbuf, yd, NR, ld, L.m2l.ldy, L.m2l.nrb * 16, (const T *)nullptr, (T *)nullptr,
-                       0, 0, (const int32_t *)P->d_m2l_rows, (const int32_t *)nullptr, (const T *)P->ydx,
-                       (const T *)nullptr);
-  FMM_HIP_TRY(hipGetLastError());
+  if ((rc = launch_m2l_sum<T>(P, nullptr, NR, NR == 1, s))) return rc;
   prof_end(P, FMM_PHASE_M2L_SUM, ev, s);
   // downward pass: L2L between singular coordinates, coarsest level first
   for (int l = 3; l <= D.maxlevel; ++l) {
@@ -2061,8 +2595,8 @@ static int pair_p2l(fmm_plan *A, fmm_plan *B, hipStream_t s, const T *dips) {
 constexpr unsigned CHAIN_SPIN_LIMIT = 1u << 18;  // polls (a memory round trip and ~128 cycles each)
 
 template <typename T, int NR>
-static int build_chain(fmm_plan *A, fmm_plan *B, bool up, Chain &C) {
-  const PassLists &LA = A->lists_by_nr[NR], &LB = B->lists_by_nr[NR];
+static int build_chain(fmm_plan *A, fmm_plan *B, bool keeps, bool up, Chain &C) {
+  const PassLists &LA = A->lists[op_set(A, keeps)][NR], &LB = B->lists[op_set(B, keeps)][NR];
   const DevTree &D = A->dt;
   std::vector<ChainTask> tasks;
   std::vector<GemmArgs> ga;
@@ -2130,15 +2664,16 @@ static int build_chain(fmm_plan *A, fmm_plan *B, bool up, Chain &C) {
 // Both chains current for (A, B, NR) and a counter array for them (ticket
 // and phase counters of each chain, then the error flag).
 template <typename T, int NR>
-static int ensure_chains(fmm_plan *A, fmm_plan *B) {
+static int ensure_chains(fmm_plan *A, fmm_plan *B, bool keeps) {
+  Chain &up = A->chain_up[keeps], &down = A->chain_down[keeps];
   const std::vector<const void *> key = {B, (const void *)(intptr_t)NR, A->cu, A->mslot, A->yd, B->cu, B->mslot, B->yd};
   int rc;
-  if (A->chain_up.key != key) {
-    if ((rc = build_chain<T, NR>(A, B, true, A->chain_up))) return rc;
-    if ((rc = build_chain<T, NR>(A, B, false, A->chain_down))) return rc;
-    A->chain_up.key = A->chain_down.key = key;
+  if (up.key != key) {
+    if ((rc = build_chain<T, NR>(A, B, keeps, true, up))) return rc;
+    if ((rc = build_chain<T, NR>(A, B, keeps, false, down))) return rc;
+    up.key = down.key = key;
   }
-  const int n = 2 + A->chain_up.nphase + A->chain_down.nphase + 1;
+  const int n = 2 + up.nphase + down.nphase + 1;
   if (A->chain_ctr_n < n) {
     std::vector<int32_t> z(n, 0);
     if ((rc = plan_upload(A, (void **)&A->chain_ctr, z.data(), z.size() * sizeof(int32_t)))) return rc;
@@ -2177,7 +2712,7 @@ static int eval_passes_pair(fmm_plan *A, fmm_plan *B, hipStream_t s, int part, h
   const DevTree &D = A->dt;
   const int64_t N = A->n;
   const int ld = A->ld;
-  const PassLists &LA = A->lists_by_nr[NR], &LB = B->lists_by_nr[NR];
+  const PassLists &LA = A->lists[op_set(A, dips != nullptr)][NR], &LB = B->lists[op_set(B, dips != nullptr)][NR];
   const T *qs = (const T *)A->qs;
   auto W = [](void *p) { return (T *)p; };
   const T kappa = (T)B->kappa;
@@ -2185,9 +2720,10 @@ static int eval_passes_pair(fmm_plan *A, fmm_plan *B, hipStream_t s, int part, h
   hipEvent_t ev;
   if (D.maxlevel < 2) return FMM_OK;
   // chained M2M and L2L launches (built for this pair and column count)
-  const bool chain = A->tune.gemm_chain && A->chain_ctr && !A->chain_up.key.empty() && A->chain_up.key[0] == B &&
-                     A->chain_up.key[1] == (const void *)(intptr_t)NR;
-  int32_t *ctr_up = A->chain_ctr, *ctr_down = A->chain_ctr + 1 + A->chain_up.nphase,
+  const Chain &cup = A->chain_up[dips != nullptr], &cdown = A->chain_down[dips != nullptr];
+  const bool chain = A->tune.gemm_chain && A->chain_ctr && !cup.key.empty() && cup.key[0] == B &&
+                     cup.key[1] == (const void *)(intptr_t)NR;
+  int32_t *ctr_up = A->chain_ctr, *ctr_down = A->chain_ctr + 1 + cup.nphase,
           *chain_err = A->chain_ctr + A->chain_ctr_n - 1;
   if (part == 2) goto down;
   {
@@ -2195,19 +2731,10 @@ static int eval_passes_pair(fmm_plan *A, fmm_plan *B, hipStream_t s, int part, h
   // level ls is done (the upward coordinates of every box at those levels
   // are then final), beside the coarser M2M levels; the coarser levels' M2L
   // follows on s, which then waits for s3.  M2L tasks ascend by level.
-  const bool fact = LA.m2l_r.ntask > 0 || LB.m2l_r.ntask > 0;
   const int ls = D.maxlevel - 1;
   // (s3 may be the null stream: split_m2l, not s3, says whether to split)
-  const bool m2l_early = split_m2l && A->tune.m2l_early && !chain && !fact && ls >= 2 &&
-                         LA.m2l_t0.size() == (size_t)D.maxlevel + 2 && LB.m2l_t0.size() == (size_t)D.maxlevel + 2;
-  auto m2l_levels = [&](int l0, int l1, hipStream_t st) -> int {  // the M2L of levels [l0, l1)
-    GemmBatch a = LA.m2l, b = LB.m2l;
-    a.d_tasks += LA.m2l_t0[l0];
-    a.ntask = LA.m2l_t0[l1] - LA.m2l_t0[l0];
-    b.d_tasks += LB.m2l_t0[l0];
-    b.ntask = LB.m2l_t0[l1] - LB.m2l_t0[l0];
-    return launch_gemm2<T>(A, a, W(A->cu), W(A->pairbuf), B, &b, W(B->cu), W(B->pairbuf), st);
-  };
+  const bool m2l_early = split_m2l && A->tune.m2l_early && !chain && !A->tune.m2l_factored &&
+                         !B->tune.m2l_factored && ls >= 2;
   if (chain) {
     hipLaunchKernelGGL(k_fill_zero<int32_t>, dim3(1), dim3(256), 0, s, A->chain_ctr, (int64_t)A->chain_ctr_n - 1);
     FMM_HIP_TRY(hipGetLastError());
@@ -2231,12 +2758,12 @@ static int eval_passes_pair(fmm_plan *A, fmm_plan *B, hipStream_t s, int part, h
   if ((rc = launch_gemm2<T>(A, LA.ut_u_all, W(A->chku), W(A->cu), B, &LB.ut_u_all, W(B->chku), W(B->cu), s)))
     return rc;
   prof_end(A, FMM_PHASE_UC2E, ev, s);
-  if (chain && A->chain_up.ntask) {
+  if (chain && cup.ntask) {
     ev = prof_begin(A, FMM_PHASE_M2M, s);
-    if ((rc = launch_chain<T>(A->chain_up, ctr_up, chain_err, s))) return rc;
+    if ((rc = launch_chain<T>(cup, ctr_up, chain_err, s))) return rc;
     prof_end(A, FMM_PHASE_M2M, ev, s);
   }
-  for (int l = D.maxlevel - 1; l >= 2 && !(chain && A->chain_up.ntask); --l) {
+  for (int l = D.maxlevel - 1; l >= 2 && !(chain && cup.ntask); --l) {
     if (LA.m2m[l].ntask) {
       ev = prof_begin(A, FMM_PHASE_M2M, s);
       if ((rc = launch_gemm2<T>(A, LA.m2m[l], W(A->cu), W(A->mslot), B, &LB.m2m[l], W(B->cu), W(B->mslot), s)))
@@ -2252,7 +2779,7 @@ static int eval_passes_pair(fmm_plan *A, fmm_plan *B, hipStream_t s, int part, h
       FMM_HIP_TRY(hipEventRecord(A->ev_m2m, s));
       FMM_HIP_TRY(hipStreamWaitEvent(s3, A->ev_m2m, 0));
       ev = prof_begin(A, FMM_PHASE_M2L, s3);
-      if ((rc = m2l_levels(ls, D.maxlevel + 1, s3))) return rc;
+      if ((rc = launch_m2l_form<T>(A, B, NR, dips != nullptr, ls, D.maxlevel + 1, s3))) return rc;
       prof_end(A, FMM_PHASE_M2L, ev, s3);
       FMM_HIP_TRY(hipEventRecord(A->ev_m2lf, s3));
     }
@@ -2260,21 +2787,11 @@ static int eval_passes_pair(fmm_plan *A, fmm_plan *B, hipStream_t s, int part, h
   if (up_done) FMM_HIP_TRY(hipEventRecord(up_done, s));
   ev = prof_begin(A, FMM_PHASE_M2L, s);
   if (m2l_early) {
-    if ((rc = m2l_levels(0, ls, s))) return rc;
+    if ((rc = launch_m2l_form<T>(A, B, NR, dips != nullptr, 0, ls, s))) return rc;
     prof_end(A, FMM_PHASE_M2L, ev, s);
     FMM_HIP_TRY(hipStreamWaitEvent(s, A->ev_m2lf, 0));
   } else {
-    // a factored plan first maps its upward coordinates through R (one
-    // launch for the factored plans), then every plan's L (or dense operator)
-    // writes the pair slots
-    const bool fa = LA.m2l_r.ntask > 0, fb = LB.m2l_r.ntask > 0;
-    rc = FMM_OK;
-    if (fa) rc = launch_gemm2<T>(A, LA.m2l_r, W(A->cu), W(A->m2l_t), fb ? B : nullptr, &LB.m2l_r, W(B->cu), W(B->m2l_t), s);
-    else if (fb) rc = launch_gemm<T>(B, LB.m2l_r, W(B->cu), W(B->m2l_t), s);
-    if (rc) return rc;
-    if ((rc = launch_gemm2<T>(A, LA.m2l, fa ? W(A->m2l_t) : W(A->cu), W(A->pairbuf), B, &LB.m2l,
-                              fb ? W(B->m2l_t) : W(B->cu), W(B->pairbuf), s)))
-      return rc;
+    if ((rc = launch_m2l_form<T>(A, B, NR, dips != nullptr, 0, D.maxlevel + 1, s))) return rc;
     prof_end(A, FMM_PHASE_M2L, ev, s);
   }
   }
@@ -2283,21 +2800,16 @@ down:
   // the M2L sums add the P2L projections (`ydx`, computed on another stream
   // by pair_p2l_projection and waited for by the caller)
   ev = prof_begin(A, FMM_PHASE_M2L_SUM, s);
-  if (D.nvbox > 0)
-    hipLaunchKernelGGL(k_pair_reduce<T>, dim3(D.nvbox, 2), dim3(64), 0, s, D.v_tgt, D.v_off, D.v_pair,
-                       (const T *)A->pairbuf, W(A->yd), NR, ld, LA.m2l.ldy, LA.m2l.nrb * 16, (const T *)B->pairbuf,
-                       W(B->yd), LB.m2l.ldy, LB.m2l.nrb * 16, (const int32_t *)A->d_m2l_rows,
-                       (const int32_t *)B->d_m2l_rows, (const T *)A->ydx, (const T *)B->ydx);
-  FMM_HIP_TRY(hipGetLastError());
+  if ((rc = launch_m2l_sum<T>(A, B, NR, dips != nullptr, s))) return rc;
   prof_end(A, FMM_PHASE_M2L_SUM, ev, s);
-  if (chain && A->chain_down.ntask) {
+  if (chain && cdown.ntask) {
     ev = prof_begin(A, FMM_PHASE_L2L, s);
-    if ((rc = launch_chain<T>(A->chain_down, ctr_down, chain_err, s))) return rc;
+    if ((rc = launch_chain<T>(cdown, ctr_down, chain_err, s))) return rc;
     prof_end(A, FMM_PHASE_L2L, ev, s);
   }
   // with gemm_narrow the downward passes use one-wave workgroups, which
   // find room beside the near field's waves (pass orders 3 and 4 run them there)
-  for (int l = 3; l <= D.maxlevel && !(chain && A->chain_down.ntask); ++l) {
+  for (int l = 3; l <= D.maxlevel && !(chain && cdown.ntask); ++l) {
     if (!LA.l2l[l].ntask) continue;
     ev = prof_begin(A, FMM_PHASE_L2L, s);
     rc = A->tune.gemm_narrow
@@ -2360,7 +2872,8 @@ static int eval_typed(fmm_plan *P, const T *q, int nrhs, T *pot, T *grad, hipStr
     const int nr = std::min(MAX_NR, nrhs - c0);
     int rc;
     if ((rc = ensure_work(P, nr))) return rc;
-    if ((rc = ensure_lists(P, nr))) return rc;
+    if ((rc = ensure_lists(P, nr, op_set(P, nr == 1)))) return rc;
+    if ((rc = ensure_m2l(P, nr, op_set(P, nr == 1)))) return rc;
     const T *qc = q + (int64_t)c0 * N;
     T *pc = pot + (int64_t)c0 * N;
     T *gc = grad ? grad + (int64_t)c0 * N * 3 : nullptr;
@@ -2389,7 +2902,7 @@ int ensure_pair(fmm_plan *A, fmm_plan *B, int nr);  // host: side streams, event
 // B's join event marks their end.
 template <typename T, int NR>
 static int pair_p2l_proj(fmm_plan *A, fmm_plan *B, hipStream_t s, const T *dips) {
-  const PassLists &LA = A->lists_by_nr[NR], &LB = B->lists_by_nr[NR];
+  const PassLists &LA = A->lists[op_set(A, dips != nullptr)][NR], &LB = B->lists[op_set(B, dips != nullptr)][NR];
   int rc = pair_p2l<T, NR>(A, B, s, dips);
   if (rc) return rc;
   hipEvent_t ev = prof_begin(A, FMM_PHASE_DC2E, s);
@@ -2402,7 +2915,7 @@ static int pair_p2l_proj(fmm_plan *A, fmm_plan *B, hipStream_t s, const T *dips)
 
 template <typename T, int NR>
 static int pair_off_chain(fmm_plan *A, fmm_plan *B, hipStream_t s, const T *dips, bool p2l, bool vsu = true) {
-  const PassLists &LA = A->lists_by_nr[NR], &LB = B->lists_by_nr[NR];
+  const PassLists &LA = A->lists[op_set(A, dips != nullptr)][NR], &LB = B->lists[op_set(B, dips != nullptr)][NR];
   int rc;
   if (p2l && (rc = pair_p2l_proj<T, NR>(A, B, s, dips))) return rc;
   if (!vsu) return FMM_OK;
@@ -2529,7 +3042,7 @@ static int eval_pair_chunk(fmm_plan *A, fmm_plan *B, const T *q, T *pot_a, T *gr
     return FMM_OK;
   };
 
-  if (A->tune.gemm_chain && D.maxlevel >= 2 && (rc = ensure_chains<T, NR>(A, B))) return rc;
+  if (A->tune.gemm_chain && D.maxlevel >= 2 && (rc = ensure_chains<T, NR>(A, B, false))) return rc;
   if ((rc = pair_fork_join<T, NR>(A, B, s, (const T *)nullptr, near))) return rc;
   hipEvent_t ev = prof_begin(A, FMM_PHASE_FAR, s);
   if (D.nitems > 0)
@@ -2555,8 +3068,9 @@ static int eval_pair_typed(fmm_plan *A, fmm_plan *B, const T *q, int nrhs, T *po
   for (int c0 = 0; c0 < nrhs; c0 += MAX_NR) {
     const int nr = std::min(MAX_NR, nrhs - c0);
     int rc;
-    if ((rc = ensure_work(A, nr)) || (rc = ensure_lists(A, nr)) || (rc = ensure_work(B, nr)) ||
-        (rc = ensure_lists(B, nr)) || (rc = ensure_pair(A, B, nr)))
+    const int sa = op_set(A, false), sb = op_set(B, false);
+    if ((rc = ensure_work(A, nr)) || (rc = ensure_lists(A, nr, sa)) || (rc = ensure_work(B, nr)) ||
+        (rc = ensure_lists(B, nr, sb)) || (rc = ensure_m2l(A, nr, sa)) || (rc = ensure_m2l(B, nr, sb)) || (rc = ensure_pair(A, B, nr)))
       return rc;
     const T *qc = q + (int64_t)c0 * N;
     T *pa = pot_a + (int64_t)c0 * N, *pb = pot_b + (int64_t)c0 * N;
@@ -2591,8 +3105,9 @@ static int eval_pair_md_typed(fmm_plan *A, fmm_plan *B, const T *q, const T *dip
                               T *pot_b, T *grad_b, hipStream_t s) {
   const bool grad = grad_a || grad_b;
   int rc;
-  if ((rc = ensure_work(A, 1)) || (rc = ensure_lists(A, 1)) || (rc = ensure_work(B, 1)) ||
-      (rc = ensure_lists(B, 1)) || (rc = ensure_pair(A, B, 1)) || (rc = ensure_pair_md(A, B)))
+  const int sa = op_set(A, true), sb = op_set(B, true);
+  if ((rc = ensure_work(A, 1)) || (rc = ensure_lists(A, 1, sa)) || (rc = ensure_work(B, 1)) ||
+      (rc = ensure_lists(B, 1, sb)) || (rc = ensure_m2l(A, 1, sa)) || (rc = ensure_m2l(B, 1, sb)) || (rc = ensure_pair(A, B, 1)) || (rc = ensure_pair_md(A, B)))
     return rc;
   const DevTree &D = A->dt;
   const int64_t N = A->n;
@@ -2620,7 +3135,7 @@ static int eval_pair_md_typed(fmm_plan *A, fmm_plan *B, const T *q, const T *dip
     FMM_HIP_TRY(hipGetLastError());
     return FMM_OK;
   };
-  if (A->tune.gemm_chain && D.maxlevel >= 2 && (rc = ensure_chains<T, 1>(A, B))) return rc;
+  if (A->tune.gemm_chain && D.maxlevel >= 2 && (rc = ensure_chains<T, 1>(A, B, true))) return rc;
   if ((rc = pair_fork_join<T, 1>(A, B, s, (const T *)dips, near))) return rc;
   ev = prof_begin(A, FMM_PHASE_FAR, s);
   if (D.nitems > 0 && grad)
