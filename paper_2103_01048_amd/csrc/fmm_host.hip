@@ -1447,11 +1447,19 @@ int ensure_pair_md(fmm_plan *A, fmm_plan *B) {
 }
 
 int ensure_work(fmm_plan *P, int nr) {
-  if (P->work_nr >= nr) return FMM_OK;
   const size_t es = P->precision == FMM_FP64 ? 8 : 4;
   const int64_t nb = P->dt.nbox;
   const size_t wbytes = (size_t)nb * nr * P->ld * es;
   int rc;
+  // rows of boxes without an X list stay zero, as the M2L sums add this array;
+  // a box's rows depend on the number of columns, so each number has its own
+  if (!P->ydx[nr]) {
+    void *a = nullptr;
+    if ((rc = dev_alloc(P, &a, wbytes))) return rc;
+    FMM_HIP_TRY(hipMemset(a, 0, wbytes));
+    P->ydx[nr] = a;
+  }
+  if (P->work_nr >= nr) return FMM_OK;
   // old buffers stay in allocs until fmm_free (simple and safe for in-flight work)
   if ((rc = dev_alloc(P, &P->qs, (size_t)P->n * nr * es))) return rc;
   if ((rc = dev_alloc(P, &P->equ, wbytes))) return rc;
@@ -1463,7 +1471,6 @@ int ensure_work(fmm_plan *P, int nr) {
   if ((rc = dev_alloc(P, &P->cu, cbytes))) return rc;
   if ((rc = dev_alloc(P, &P->yd, wbytes))) return rc;
   if ((rc = dev_alloc(P, &P->mslot, wbytes))) return rc;
-  if ((rc = dev_alloc(P, &P->ydx, wbytes))) return rc;
   // padding rows/columns must hold zeros (the GEMM K dimension reads them)
   FMM_HIP_TRY(hipMemset(P->equ, 0, wbytes));
   FMM_HIP_TRY(hipMemset(P->chk, 0, wbytes));
@@ -1471,8 +1478,6 @@ int ensure_work(fmm_plan *P, int nr) {
   FMM_HIP_TRY(hipMemset(P->chku, 0, wbytes));
   FMM_HIP_TRY(hipMemset(P->cu, 0, cbytes));
   FMM_HIP_TRY(hipMemset(P->yd, 0, wbytes));
-  // rows of boxes without an X list stay zero: the M2L sums add this array
-  FMM_HIP_TRY(hipMemset(P->ydx, 0, wbytes));
   P->work_nr = nr;
   return FMM_OK;
 }

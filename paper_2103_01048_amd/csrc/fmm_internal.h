@@ -301,10 +301,11 @@ struct fmm_plan {
   // work arrays, sized for work_nr columns
   int work_nr = 0, colbuf_nr = 0, pairbuf_nr = 0;
   void *qs = nullptr, *equ = nullptr, *chk = nullptr, *eqd = nullptr, *chku = nullptr,
-       *cu = nullptr, *yd = nullptr, *pairbuf = nullptr, *colbuf = nullptr, *cub = nullptr, *mslot = nullptr, *ydx = nullptr, *m2l_t = nullptr;
+       *cu = nullptr, *yd = nullptr, *pairbuf = nullptr, *colbuf = nullptr, *cub = nullptr, *mslot = nullptr, *m2l_t = nullptr;
   // cub: cu split into bf16 high and low parts (bf16x3, segmented M2L)
   // cu: upward check in singular coordinates (U_u^T chk); yd: downward
   // check in singular coordinates (M2L sums + U_d^T chk)
+  void *ydx[fmm::MAX_NR + 1] = {};  // P2L projections, by the number of columns
   fmm::PassLists lists[2][fmm::MAX_NR + 1];  // task lists per operator set and column count
   // P2M targets (leaves at level >= 2) and per-leaf flags
   int p2m_count = 0;

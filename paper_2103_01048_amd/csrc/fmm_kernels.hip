@@ -2460,7 +2460,7 @@ static int launch_m2l_sum(fmm_plan *P, fmm_plan *Q, int nr, bool keeps_order, hi
                        ldp(A), rows(A), B ? slots(B) : nullptr, B ? (T *)B->yd : nullptr, B ? ldp(B) : 0,
                        B ? rows(B) : 0, (const int32_t *)A->lists[pw][nr].d_m2l_rows,
                        B ? (const int32_t *)B->lists[pw][nr].d_m2l_rows : nullptr,
-                       (const T *)A->ydx, B ? (const T *)B->ydx : nullptr);
+                       (const T *)A->ydx[nr], B ? (const T *)B->ydx[nr] : nullptr);
   };
   if (!Q || pp == pq) {
     go(P, Q, pp);
@@ -2536,7 +2536,7 @@ static int eval_passes(fmm_plan *P, hipStream_t s) {
   prof_end(P, FMM_PHASE_P2L, ev, s);
   // the P2L checks' projections go to their own array, added by the M2L sums
   ev = prof_begin(P, FMM_PHASE_DC2E, s);
-  if ((rc = launch_gemm<T>(P, L.ut_dx, chk, (T *)P->ydx, s))) return rc;
+  if ((rc = launch_gemm<T>(P, L.ut_dx, chk, (T *)P->ydx[NR], s))) return rc;
   prof_end(P, FMM_PHASE_DC2E, ev, s);
   // M2L between singular coordinates into slots (rows of the largest
   // downward rank, not of the surface size), then a fixed-order sum per
@@ -2906,7 +2906,7 @@ static int pair_p2l_proj(fmm_plan *A, fmm_plan *B, hipStream_t s, const T *dips)
   int rc = pair_p2l<T, NR>(A, B, s, dips);
   if (rc) return rc;
   hipEvent_t ev = prof_begin(A, FMM_PHASE_DC2E, s);
-  rc = launch_gemm2<T>(A, LA.ut_dx, (const T *)A->chk, (T *)A->ydx, B, &LB.ut_dx, (const T *)B->chk, (T *)B->ydx, s);
+  rc = launch_gemm2<T>(A, LA.ut_dx, (const T *)A->chk, (T *)A->ydx[NR], B, &LB.ut_dx, (const T *)B->chk, (T *)B->ydx[NR], s);
   if (rc) return rc;
   prof_end(A, FMM_PHASE_DC2E, ev, s);
   FMM_HIP_TRY(hipEventRecord(B->ev_join, s));

@@ -57,3 +57,21 @@ def test_segmented_m2l(precision, tol, p, n_tri, ncrit):
     four = eval_pair(plans[0], plans[1], q)
     for (pot, grad), (pot4, grad4) in zip(one, four):
         assert _rel(pot4[0], pot) < (tol or 1e-12) and _rel(grad4[0], grad) < (tol or 1e-12)
+
+
+def test_one_column_after_four_keeps_its_bits():
+    """Rows that a four-column evaluation wrote must not show in a one-column one."""
+    torch = require_gpu()
+    from paper_2103_01048_amd import FMMPlan, eval_pair
+    x = torch.tensor(_cloud(1500, seed=143), device="cuda")
+    q = torch.tensor(np.random.default_rng(144).standard_normal((4, len(x))), device="cuda", dtype=torch.float32)
+    for precision in ("fp32", "bf16x3"):
+        pl = [FMMPlan(x, kernel=k, kappa=KAPPA, p=6, ncrit=32, precision=precision) for k in ("laplace", "yukawa")]
+        first = [t.clone() for o in eval_pair(pl[0], pl[1], q[0]) for t in o]
+        alone = [t.clone() for t in pl[1].eval(q[0])]
+        eval_pair(pl[0], pl[1], q)
+        pl[1].eval(q)
+        for u, w in zip(first, [t for o in eval_pair(pl[0], pl[1], q[0]) for t in o]):
+            assert torch.equal(u, w)
+        for u, w in zip(alone, pl[1].eval(q[0])):
+            assert torch.equal(u, w)
