@@ -1177,6 +1177,18 @@ __device__ inline void pair_gf(T r2, T kappa, T &g, T &f) {
 // different Morton cells; surfaces never touch the targets they serve),
 // and a range counts as holding it when it overlaps the leaf's points.
 // Writes potential (and gradient) times `scale` in the caller's order.
+// Bound by vector instructions, with few waves by the latency at the head of
+// each range.  Sub-waves therefore test for a missing source only in a range's
+// last step: the whole steps' loads take a uniform base and no selects (six of
+// about 31 instructions a step).  The next range's bounds and shift are loaded
+// while a range is summed.  Unrolled by 4 (FP64 2: registers).  Same sums in
+// the same order as with a test in each step; passes with that / with this:
+// 9000-point pair evaluation 301 / 275 us, 393216-point pair evaluation 1083 /
+// 1045 us, 100003-point Yukawa sum of 4 columns 805 / 726 us, potential and
+// adjoint of 1000002 points 4270 / 4092 us.  Not taken: a tile's remainder of
+// targets in power-of-two segments (lanes in use 0.70 -> 0.85 at 20 points per
+// leaf): the far field alone 85 -> 57 us, but the whole steps above give as much
+// without a second pass over the ranges.
 template <typename T, int KERN, bool CHECK, int NR>
 __device__ __forceinline__ void leaf_pair(T xi, T yi, T zi, T sx, T sy, T sz, const T (&qv)[NR], T kappa, T kl2,
                                           T (&ap)[NR], T (&agx)[NR], T (&agy)[NR], T (&agz)[NR]) {
@@ -1203,6 +1215,47 @@ __device__ __forceinline__ void leaf_pair(T xi, T yi, T zi, T sx, T sy, T sz, co
   }
 }
 
+// Sum over the sub-waves of a tile, the upper half onto the lower first.
+template <typename T, int NR>
+__device__ __forceinline__ void subwave_sum(int split, T (&v)[NR]) {
+  for (int o = 32; o >= 64 / split; o >>= 1)
+#pragma unroll
+    for (int c = 0; c < NR; ++c) v[c] += __shfl_xor(v[c], o);
+}
+
+template <typename T, int NR>
+__device__ __forceinline__ void leaf_store(int part, int sub, bool active, int tl, int tb, T *__restrict__ parts,
+                                           const int32_t *__restrict__ perm, int64_t N, T *__restrict__ pot,
+                                           T *__restrict__ grad, T scale, const T (&ap)[NR], const T (&agx)[NR],
+                                           const T (&agy)[NR], const T (&agz)[NR]) {
+  if (part >= 0) {
+    if (sub == 0) {
+      T *pp = parts + (int64_t)part * NR * 4 * 64;
+#pragma unroll
+      for (int c = 0; c < NR; ++c) {
+        pp[(c * 4 + 0) * 64 + tl] = ap[c];
+        pp[(c * 4 + 1) * 64 + tl] = agx[c];
+        pp[(c * 4 + 2) * 64 + tl] = agy[c];
+        pp[(c * 4 + 3) * 64 + tl] = agz[c];
+      }
+    }
+    return;
+  }
+  if (active && sub == 0) {
+    const int64_t o = perm[tb + tl];
+#pragma unroll
+    for (int c = 0; c < NR; ++c) {
+      pot[(int64_t)c * N + o] = ap[c] * scale;
+      if (grad) {
+        T *gp = grad + ((int64_t)c * N + o) * 3;
+        gp[0] = agx[c] * scale;
+        gp[1] = agy[c] * scale;
+        gp[2] = agz[c] * scale;
+      }
+    }
+  }
+}
+
 template <typename T, int NR, int KERN>
 __global__ __launch_bounds__(64) void k_leaf_eval(
     const int32_t *__restrict__ items, const int32_t *__restrict__ leaves, const T *__restrict__ pts,
@@ -1224,7 +1277,7 @@ __global__ __launch_bounds__(64) void k_leaf_eval(
   const int lb = box_begin[b], le = box_end[b];
   const int tb = lb + (code & 0xffffff);
   const int lane = threadIdx.x;
-  const int sub = split == 1 ? 0 : lane / (64 / split);  // sub-wave
+  const unsigned sub = split == 1 ? 0 : lane / (64 / split);  // sub-wave
   const int tl = lane & (64 / split - 1);
   const int m = min(64 / split, le - tb);
   const bool active = tl < m;
@@ -1237,11 +1290,19 @@ __global__ __launch_bounds__(64) void k_leaf_eval(
 
   // near field: point ranges
   const int u1 = near_off[item + 1];
-  for (int u = near_off[item]; u < u1; ++u) {
-    const int j0 = near_rng[2 * u], j1 = near_rng[2 * u + 1];
+  // a range's bounds and shift are loaded while the one before is summed
+  int u = near_off[item];
+  int n0 = 0, n1 = 0;
+  T ox = 0, oy = 0, oz = 0;
+  if (u < u1) { n0 = near_rng[2 * u]; n1 = near_rng[2 * u + 1]; ox = near_o[4 * u]; oy = near_o[4 * u + 1]; oz = near_o[4 * u + 2]; }
+  for (; u < u1; ++u) {
+    const int j0 = n0, j1 = n1;
     const bool self = j0 < le && lb < j1;  // overlaps the tile's own leaf
     // targets in the source leaf's frame (one shift per range)
-    const T xt = xi - near_o[4 * u], yt = yi - near_o[4 * u + 1], zt = zi - near_o[4 * u + 2];
+    const T xt = xi - ox, yt = yi - oy, zt = zi - oz;
+    const int un = min(u + 1, u1 - 1);
+    n0 = near_rng[2 * un]; n1 = near_rng[2 * un + 1];
+    ox = near_o[4 * un]; oy = near_o[4 * un + 1]; oz = near_o[4 * un + 2];
     if (split == 1) {
       auto body = [&](int j, auto chk) {
         const V4 sp = p4[j];
@@ -1263,25 +1324,27 @@ __global__ __launch_bounds__(64) void k_leaf_eval(
     } else {
       // split into 2 or 4 sub-waves: sub-wave h takes sources j0 + h,
       // j0 + h + split, ...; a count that is not a multiple of split leaves
-      // the last steps of the upper sub-waves with a zero charge
-      auto body = [&](int j, auto chk) {
-        const int jj = j + sub;
-        const bool ok = jj < j1;
-        const V4 sp = p4[ok ? jj : j];
+      // the last step of the upper sub-waves with a zero charge
+      auto step = [&](int j, bool ok, auto chk) {
+        const unsigned o = ok ? sub : 0u;
+        const V4 sp = (p4 + j)[o];
         T qv[NR];
         if (NR == 1) qv[0] = ok ? sp[3] : (T)0;
         else {
 #pragma unroll
-          for (int c = 0; c < NR; ++c) qv[c] = ok ? qs[(int64_t)c * N + jj] : (T)0;
+          for (int c = 0; c < NR; ++c) qv[c] = ok ? (qs + (int64_t)c * N + j)[o] : (T)0;
         }
         leaf_pair<T, KERN, decltype(chk)::value, NR>(xt, yt, zt, sp[0], sp[1], sp[2], qv, kappa, kl2, ap, agx, agy, agz);
       };
+      int j = j0;
       if (self) {
 #pragma unroll 2
-        for (int j = j0; j < j1; j += split) body(j, std::true_type());
+        for (; j + split <= j1; j += split) step(j, true, std::true_type());
+        if (j < j1) step(j, j + (int)sub < j1, std::true_type());
       } else {
 #pragma unroll 4
-        for (int j = j0; j < j1; j += split) body(j, std::false_type());
+        for (; j + split <= j1; j += split) step(j, true, std::false_type());
+        if (j < j1) step(j, j + (int)sub < j1, std::false_type());
       }
     }
   }
@@ -1308,64 +1371,23 @@ __global__ __launch_bounds__(64) void k_leaf_eval(
                                       agx, agy, agz);
       }
     } else {
-#pragma unroll 2
-      for (int j = 0; j < nsurf; j += split) {
-        const int jj = j + sub;
-        const bool ok = jj < nsurf;
-        const V4 g = s4[ok ? jj : j];
+      auto step = [&](int j, bool ok) {
+        const unsigned o = ok ? sub : 0u;
+        const V4 g = (s4 + j)[o];
         T qv[NR];
 #pragma unroll
-        for (int c = 0; c < NR; ++c) qv[c] = ok ? dens[(int64_t)c * ld + jj] : (T)0;
+        for (int c = 0; c < NR; ++c) qv[c] = ok ? (dens + (int64_t)c * ld + j)[o] : (T)0;
         leaf_pair<T, KERN, false, NR>(xt, yt, zt, rr * g[0], rr * g[1], rr * g[2], qv, kappa, kl2, ap,
                                       agx, agy, agz);
-      }
+      };
+      int j = 0;
+#pragma unroll 2
+      for (; j + split <= nsurf; j += split) step(j, true);
+      if (j < nsurf) step(j, j + (int)sub < nsurf);
     }
   }
-  if (split >= 2) {
-#pragma unroll
-    for (int c = 0; c < NR; ++c) {
-      ap[c] += __shfl_xor(ap[c], 32);
-      agx[c] += __shfl_xor(agx[c], 32);
-      agy[c] += __shfl_xor(agy[c], 32);
-      agz[c] += __shfl_xor(agz[c], 32);
-    }
-  }
-  if (split == 4) {
-#pragma unroll
-    for (int c = 0; c < NR; ++c) {
-      ap[c] += __shfl_xor(ap[c], 16);
-      agx[c] += __shfl_xor(agx[c], 16);
-      agy[c] += __shfl_xor(agy[c], 16);
-      agz[c] += __shfl_xor(agz[c], 16);
-    }
-  }
-  if (part >= 0) {
-    // partial sums of a split tile: [part][column][component][lane]
-    if (sub == 0) {
-      T *pp = parts + (int64_t)part * NR * 4 * 64;
-#pragma unroll
-      for (int c = 0; c < NR; ++c) {
-        pp[(c * 4 + 0) * 64 + tl] = ap[c];
-        pp[(c * 4 + 1) * 64 + tl] = agx[c];
-        pp[(c * 4 + 2) * 64 + tl] = agy[c];
-        pp[(c * 4 + 3) * 64 + tl] = agz[c];
-      }
-    }
-    return;
-  }
-  if (active && sub == 0) {
-    const int64_t o = perm[tb + tl];
-#pragma unroll
-    for (int c = 0; c < NR; ++c) {
-      pot[(int64_t)c * N + o] = ap[c] * scale;
-      if (grad) {
-        T *gp = grad + ((int64_t)c * N + o) * 3;
-        gp[0] = agx[c] * scale;
-        gp[1] = agy[c] * scale;
-        gp[2] = agz[c] * scale;
-      }
-    }
-  }
+  subwave_sum(split, ap); subwave_sum(split, agx); subwave_sum(split, agy); subwave_sum(split, agz);
+  leaf_store<T, NR>(part, sub, active, tl, tb, parts, perm, N, pot, grad, scale, ap, agx, agy, agz);
 }
 
 // Sum of the parts of split tiles, in part order; one wave per tile.
@@ -1481,7 +1503,7 @@ __global__ __launch_bounds__(64) void k_near_pair(
     const int lb = box_begin[b], le = box_end[b];
     const int tb = lb + (code & 0xffffff);
     const int lane = threadIdx.x;
-    const int sub = split == 1 ? 0 : lane / (64 / split);  // sub-wave
+    const unsigned sub = split == 1 ? 0 : lane / (64 / split);  // sub-wave
     const int tl = lane & (64 / split - 1);
     const int m = min(64 / split, le - tb);
     const bool active = tl < m;
@@ -1492,10 +1514,19 @@ __global__ __launch_bounds__(64) void k_near_pair(
 #pragma unroll
     for (int c = 0; c < NR; ++c) pa[c] = xa[c] = ya[c] = za[c] = pb[c] = xb[c] = yb[c] = zb[c] = (T)0;
     const int u1 = near_off[item + 1];
-    for (int u = near_off[item]; u < u1; ++u) {
-      const int j0 = near_rng[2 * u], j1 = near_rng[2 * u + 1];
-      const bool self = j0 < le && lb < j1;
-      const T xt = xi - near_o[4 * u], yt = yi - near_o[4 * u + 1], zt = zi - near_o[4 * u + 2];
+    // a range's bounds and shift are loaded while the one before is summed
+    int u = near_off[item];
+    int n0 = 0, n1 = 0;
+    T ox = 0, oy = 0, oz = 0;
+    if (u < u1) { n0 = near_rng[2 * u]; n1 = near_rng[2 * u + 1]; ox = near_o[4 * u]; oy = near_o[4 * u + 1]; oz = near_o[4 * u + 2]; }
+    for (; u < u1; ++u) {
+      const int j0 = n0, j1 = n1;
+      const bool self = j0 < le && lb < j1;  // overlaps the tile's own leaf
+      // targets in the source leaf's frame (one shift per range)
+      const T xt = xi - ox, yt = yi - oy, zt = zi - oz;
+      const int un = min(u + 1, u1 - 1);
+      n0 = near_rng[2 * un]; n1 = near_rng[2 * un + 1];
+      ox = near_o[4 * un]; oy = near_o[4 * un + 1]; oz = near_o[4 * un + 2];
       if (split == 1) {
         auto body = [&](int j, auto chk) {
           const V4 sp = p4[j];
@@ -1516,25 +1547,27 @@ __global__ __launch_bounds__(64) void k_near_pair(
           for (int j = j0; j < j1; ++j) body(j, std::false_type());
         }
       } else {
-        auto body = [&](int j, auto chk) {
-          const int jj = j + sub;
-          const bool ok = jj < j1;
-          const V4 sp = p4[ok ? jj : j];
+        auto step = [&](int j, bool ok, auto chk) {
+          const unsigned o = ok ? sub : 0u;
+          const V4 sp = (p4 + j)[o];
           T qv[NR];
           if (NR == 1) qv[0] = ok ? sp[3] : (T)0;
           else {
 #pragma unroll
-            for (int c = 0; c < NR; ++c) qv[c] = ok ? qs[(int64_t)c * N + jj] : (T)0;
+            for (int c = 0; c < NR; ++c) qv[c] = ok ? (qs + (int64_t)c * N + j)[o] : (T)0;
           }
           leaf_pair_ly<T, decltype(chk)::value, NR>(xt, yt, zt, sp[0], sp[1], sp[2], qv, qv, kappa, kl2, pa, xa, ya,
                                                      za, pb, xb, yb, zb);
         };
+        int j = j0;
         if (self) {
 #pragma unroll 2
-          for (int j = j0; j < j1; j += split) body(j, std::true_type());
+          for (; j + split <= j1; j += split) step(j, true, std::true_type());
+          if (j < j1) step(j, j + (int)sub < j1, std::true_type());
         } else {
-#pragma unroll 4
-          for (int j = j0; j < j1; j += split) body(j, std::false_type());
+#pragma unroll (sizeof(T) == 8 ? 2 : 4)
+          for (; j + split <= j1; j += split) step(j, true, std::false_type());
+          if (j < j1) step(j, j + (int)sub < j1, std::false_type());
         }
       }
     }
@@ -1549,39 +1582,6 @@ __global__ __launch_bounds__(64) void k_near_pair(
       a[((NR + c) * 4 + 1) * 64 + lane] = xb[c];
       a[((NR + c) * 4 + 2) * 64 + lane] = yb[c];
       a[((NR + c) * 4 + 3) * 64 + lane] = zb[c];
-    }
-  }
-}
-
-template <typename T, int NR>
-__device__ __forceinline__ void leaf_store(int part, int sub, bool active, int tl, int tb, T *__restrict__ parts,
-                                           const int32_t *__restrict__ perm, int64_t N, T *__restrict__ pot,
-                                           T *__restrict__ grad, T scale, const T (&ap)[NR], const T (&agx)[NR],
-                                           const T (&agy)[NR], const T (&agz)[NR]) {
-  if (part >= 0) {
-    if (sub == 0) {
-      T *pp = parts + (int64_t)part * NR * 4 * 64;
-#pragma unroll
-      for (int c = 0; c < NR; ++c) {
-        pp[(c * 4 + 0) * 64 + tl] = ap[c];
-        pp[(c * 4 + 1) * 64 + tl] = agx[c];
-        pp[(c * 4 + 2) * 64 + tl] = agy[c];
-        pp[(c * 4 + 3) * 64 + tl] = agz[c];
-      }
-    }
-    return;
-  }
-  if (active && sub == 0) {
-    const int64_t o = perm[tb + tl];
-#pragma unroll
-    for (int c = 0; c < NR; ++c) {
-      pot[(int64_t)c * N + o] = ap[c] * scale;
-      if (grad) {
-        T *gp = grad + ((int64_t)c * N + o) * 3;
-        gp[0] = agx[c] * scale;
-        gp[1] = agy[c] * scale;
-        gp[2] = agz[c] * scale;
-      }
     }
   }
 }
@@ -1607,7 +1607,7 @@ __global__ __launch_bounds__(64) void k_far_pair(
   const int lb = box_begin[b], le = box_end[b];
   const int tb = lb + (code & 0xffffff);
   const int lane = threadIdx.x;
-  const int sub = split == 1 ? 0 : lane / (64 / split);  // sub-wave
+  const unsigned sub = split == 1 ? 0 : lane / (64 / split);  // sub-wave
   const int tl = lane & (64 / split - 1);
   const int m = min(64 / split, le - tb);
   const bool active = tl < m;
@@ -1660,20 +1660,22 @@ __global__ __launch_bounds__(64) void k_far_pair(
                                    ua, uxa, uya, uza, ub, uxb, uyb, uzb);
       }
     } else {
-#pragma unroll 2
-      for (int j = 0; j < nsurf; j += split) {
-        const int jj = j + sub;
-        const bool ok = jj < nsurf;
-        const V4 g = s4[ok ? jj : j];
+      auto step = [&](int j, bool ok) {
+        const unsigned o = ok ? sub : 0u;
+        const V4 g = (s4 + j)[o];
         T qa[NR], qb[NR];
 #pragma unroll
         for (int c = 0; c < NR; ++c) {
-          qa[c] = ok ? da[(int64_t)c * ld + jj] : (T)0;
-          qb[c] = ok ? db[(int64_t)c * ld + jj] : (T)0;
+          qa[c] = ok ? (da + (int64_t)c * ld + j)[o] : (T)0;
+          qb[c] = ok ? (db + (int64_t)c * ld + j)[o] : (T)0;
         }
         leaf_pair_ly<T, false, NR, GRAD>(xt, yt, zt, g[0], g[1], g[2], qa, qb, ku, ku2,
                                    ua, uxa, uya, uza, ub, uxb, uyb, uzb);
-      }
+      };
+      int j = 0;
+#pragma unroll (sizeof(T) == 8 ? 2 : 4)
+      for (; j + split <= nsurf; j += split) step(j, true);
+      if (j < nsurf) step(j, j + (int)sub < nsurf);
     }
     const T irr2 = irr * irr;
 #pragma unroll
@@ -1686,24 +1688,8 @@ __global__ __launch_bounds__(64) void k_far_pair(
       }
     }
   }
-  if (split >= 2) {
-#pragma unroll
-    for (int c = 0; c < NR; ++c) {
-      pa[c] += __shfl_xor(pa[c], 32); xa[c] += __shfl_xor(xa[c], 32);
-      ya[c] += __shfl_xor(ya[c], 32); za[c] += __shfl_xor(za[c], 32);
-      pb[c] += __shfl_xor(pb[c], 32); xb[c] += __shfl_xor(xb[c], 32);
-      yb[c] += __shfl_xor(yb[c], 32); zb[c] += __shfl_xor(zb[c], 32);
-    }
-  }
-  if (split == 4) {
-#pragma unroll
-    for (int c = 0; c < NR; ++c) {
-      pa[c] += __shfl_xor(pa[c], 16); xa[c] += __shfl_xor(xa[c], 16);
-      ya[c] += __shfl_xor(ya[c], 16); za[c] += __shfl_xor(za[c], 16);
-      pb[c] += __shfl_xor(pb[c], 16); xb[c] += __shfl_xor(xb[c], 16);
-      yb[c] += __shfl_xor(yb[c], 16); zb[c] += __shfl_xor(zb[c], 16);
-    }
-  }
+  subwave_sum(split, pa); subwave_sum(split, xa); subwave_sum(split, ya); subwave_sum(split, za);
+  subwave_sum(split, pb); subwave_sum(split, xb); subwave_sum(split, yb); subwave_sum(split, zb);
   leaf_store<T, NR>(part, sub, active, tl, tb, parts_a, perm, N, pot_a, grad_a, scale, pa, xa, ya, za);
   leaf_store<T, NR>(part, sub, active, tl, tb, parts_b, perm, N, pot_b, grad_b, scale, pb, xb, yb, zb);
 }
@@ -1903,7 +1889,7 @@ __global__ __launch_bounds__(64) void k_near_pair_md(
     const int lb = box_begin[b], le = box_end[b];
     const int tb = lb + (code & 0xffffff);
     const int lane = threadIdx.x;
-    const int sub = split == 1 ? 0 : lane / (64 / split);  // sub-wave
+    const unsigned sub = split == 1 ? 0 : lane / (64 / split);  // sub-wave
     const int tl = lane & (64 / split - 1);
     const int m = min(64 / split, le - tb);
     const bool active = tl < m;
@@ -1913,10 +1899,19 @@ __global__ __launch_bounds__(64) void k_near_pair_md(
     T pa = 0, pb = 0;
     T ga[3] = {0, 0, 0}, gb[3] = {0, 0, 0};
     const int u1 = near_off[item + 1];
-    for (int u = near_off[item]; u < u1; ++u) {
-      const int j0 = near_rng[2 * u], j1 = near_rng[2 * u + 1];
-      const bool self = j0 < le && lb < j1;
-      const T xt = xi - near_o[4 * u], yt = yi - near_o[4 * u + 1], zt = zi - near_o[4 * u + 2];
+    // a range's bounds and shift are loaded while the one before is summed
+    int u = near_off[item];
+    int n0 = 0, n1 = 0;
+    T ox = 0, oy = 0, oz = 0;
+    if (u < u1) { n0 = near_rng[2 * u]; n1 = near_rng[2 * u + 1]; ox = near_o[4 * u]; oy = near_o[4 * u + 1]; oz = near_o[4 * u + 2]; }
+    for (; u < u1; ++u) {
+      const int j0 = n0, j1 = n1;
+      const bool self = j0 < le && lb < j1;  // overlaps the tile's own leaf
+      // targets in the source leaf's frame (one shift per range)
+      const T xt = xi - ox, yt = yi - oy, zt = zi - oz;
+      const int un = min(u + 1, u1 - 1);
+      n0 = near_rng[2 * un]; n1 = near_rng[2 * un + 1];
+      ox = near_o[4 * un]; oy = near_o[4 * un + 1]; oz = near_o[4 * un + 2];
       if (split == 1) {
         if (self) {
 #pragma unroll 4
@@ -1928,19 +1923,21 @@ __global__ __launch_bounds__(64) void k_near_pair_md(
       } else {
         // split into sub-waves: sub-wave h takes sources j0 + h, j0 + h +
         // split, ...; a missing last source counts with zero strength
-        auto body = [&](int j, auto chk) {
-          const int jj = j + sub;
-          const bool ok = jj < j1;
-          V4 sp = p4[ok ? jj : j], sd = d4[ok ? jj : j];
+        auto step = [&](int j, bool ok, auto chk) {
+          const unsigned o = ok ? sub : 0u;
+          V4 sp = (p4 + j)[o], sd = (d4 + j)[o];
           if (!ok) { sp[3] = (T)0; sd = V4{0, 0, 0, 0}; }
           leaf_pair_md<T, decltype(chk)::value, GRAD>(xt, yt, zt, sp, sd, kappa, kl2, pa, pb, ga, gb);
         };
+        int j = j0;
         if (self) {
 #pragma unroll 2
-          for (int j = j0; j < j1; j += split) body(j, std::true_type());
+          for (; j + split <= j1; j += split) step(j, true, std::true_type());
+          if (j < j1) step(j, j + (int)sub < j1, std::true_type());
         } else {
-#pragma unroll 4
-          for (int j = j0; j < j1; j += split) body(j, std::false_type());
+#pragma unroll (sizeof(T) == 8 ? 2 : 4)
+          for (; j + split <= j1; j += split) step(j, true, std::false_type());
+          if (j < j1) step(j, j + (int)sub < j1, std::false_type());
         }
       }
     }
