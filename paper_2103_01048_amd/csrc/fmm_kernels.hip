@@ -1127,16 +1127,20 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   }
 }
 
-// Upward coordinates split into bf16 high and low parts (x = hi + lo), rows
-// [row0, row1) of row length ld; blockIdx.y = 1: a second plan's.
+// Upward coordinates split into bf16 high and low parts (x = hi + lo), the
+// `count` values from `first` on; blockIdx.y = 1: a second plan's.  The low
+// parts start lo0 / lo1 values after the high ones: each plan's buffer is sized
+// for the columns that plan has met.
 __global__ __launch_bounds__(256) void k_split_bf3(const float *__restrict__ x0, unsigned short *__restrict__ y0,
-                                                   const float *__restrict__ x1, unsigned short *__restrict__ y1,
-                                                   int64_t first, int64_t count, int64_t lo) {
+                                                   int64_t lo0, const float *__restrict__ x1,
+                                                   unsigned short *__restrict__ y1, int64_t lo1, int64_t first,
+                                                   int64_t count) {
   typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
   const int64_t i = 4 * (blockIdx.x * 256ll + threadIdx.x);
   if (i >= count) return;
   const float *__restrict__ x = (blockIdx.y ? x1 : x0) + first;
   unsigned short *__restrict__ y = (blockIdx.y ? y1 : y0) + first;
+  const int64_t lo = blockIdx.y ? lo1 : lo0;
   const floatx4 v = *reinterpret_cast<const floatx4 *>(x + i);
   const bf16x4 h = __builtin_convertvector(v, bf16x4);
   *reinterpret_cast<bf16x4 *>(y + i) = h;
@@ -2364,7 +2368,6 @@ static int launch_m2l(fmm_plan *P, fmm_plan *Q, int nr, int l0, int l1, hipStrea
   M2LArgs g0 = args(P), g1 = g0;
   g1.ntask = 0;
   if (Q) g1 = args(Q);
-  if (g0.ntask == 0) { std::swap(g0, g1); g1.ntask = 0; }
   if (g0.ntask == 0) return FMM_OK;
   const int nrb = std::max(g0.nrb, g1.ntask ? g1.nrb : 0);
   const int nt = P->lists[0][nr].m2lc.nt;
@@ -2376,12 +2379,14 @@ static int launch_m2l(fmm_plan *P, fmm_plan *Q, int nr, int l0, int l1, hipStrea
   // rows over the grid.
   if (P->precision == FMM_FP32_BF16X3) {
     // the boxes of the levels [l0, l1); a row past the last box stays zero
+    // (both plans share the tree, so their rows and their task counts agree)
     const int64_t first = P->level_begin[std::min<int>(l0, P->dt.maxlevel + 1)] * nr * P->ld;
     const int64_t count = P->level_begin[l1] * nr * P->ld - first;
     if (count > 0)
       hipLaunchKernelGGL(k_split_bf3, dim3((unsigned)((count / 4 + 255) / 256), Q ? 2 : 1), dim3(256), 0, s,
-                         (const float *)P->cu, (unsigned short *)P->cub, Q ? (const float *)Q->cu : nullptr,
-                         Q ? (unsigned short *)Q->cub : nullptr, first, count, g0.xlo);
+                         (const float *)P->cu, (unsigned short *)P->cub, g0.xlo,
+                         Q ? (const float *)Q->cu : nullptr, Q ? (unsigned short *)Q->cub : nullptr, g1.xlo, first,
+                         count);
     FMM_HIP_TRY(hipGetLastError());
   }
   // Waves x row blocks per wave, columns and k chunk of a workgroup.  Single

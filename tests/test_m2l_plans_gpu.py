@@ -1,0 +1,59 @@
+"""The segmented M2L of two plans that differ in what they have met or in how
+they were set up: the evaluations that each did alone before, the tunables
+each was set up under, and the plans whose operators they took."""
+import numpy as np
+import pytest
+
+import synth
+from tests.gpu_util import require_gpu
+
+pytestmark = pytest.mark.gpu
+KAPPA = 0.125
+
+
+def _cloud(n_tri=1500, seed=161):
+    su = synth.sphere_union_spheres(30, seed=seed, box=14.0)
+    v, t = synth.sphere_union_mesh(su, n_tri, seed=seed)
+    return synth.three_point_cloud(v, t)
+
+
+def _plans(xt, precision, **kw):
+    from paper_2103_01048_amd import FMMPlan
+    kw = {"p": 6, "ncrit": 32, **kw}
+    return [FMMPlan(xt, kernel=k, kappa=KAPPA, precision=precision, **kw) for k in ("laplace", "yukawa")]
+
+
+def _m2l_columns(plan):
+    """M2L columns of a plan: source parents of each target box."""
+    t = plan.tree()
+    return sum(len({int(t["parent"][a]) for a in v}) for v in t["V"])
+
+
+def _pair(plans, q):
+    from paper_2103_01048_amd import eval_pair
+    return [t.clone() for o in eval_pair(plans[0], plans[1], q) for t in o]
+
+
+@pytest.mark.parametrize("precision", ["bf16x3", "fp32", "fp64"])
+@pytest.mark.parametrize("first,cols", [(0, 4), (1, 4), (0, 2), (1, 3)])
+def test_pair_after_one_plan_met_more_columns(precision, first, cols):
+    """Each plan's buffers are sized for the columns that it has met; the pair
+    evaluation is the same to the bit as on plans that met nothing before."""
+    torch = require_gpu()
+    xt = torch.tensor(_cloud(), device="cuda")
+    dt = torch.float64 if precision == "fp64" else torch.float32
+    q = torch.tensor(np.random.default_rng(162).standard_normal((4, len(xt))), device="cuda", dtype=dt)
+    print(f"[m2l plans] {precision} plan {first} first, {cols} columns", flush=True)
+    plans = _plans(xt, precision)
+    assert _m2l_columns(plans[0]) >= 1024  # enough for the segmented form
+    want = _pair(plans, q[0])
+    del plans
+    plans = _plans(xt, precision)
+    plans[first].eval(q[:cols])
+    for _ in range(2):
+        for got, ref in zip(_pair(plans, q[0]), want):
+            assert torch.equal(got, ref)
+    # and two columns after it, where only one plan's buffers grow or none do
+    want = _pair(_plans(xt, precision), q[1:3])
+    for got, ref in zip(_pair(plans, q[1:3]), want):
+        assert torch.equal(got, ref)
