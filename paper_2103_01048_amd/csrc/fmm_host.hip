@@ -1195,9 +1195,8 @@ int ensure_lists(fmm_plan *P, int nr, int set) {
   PassLists &L = P->lists[set][nr];
   if (L.nr == nr) return FMM_OK;
   if (P->n > 0 && !O.built) {
-    // an operator's plan evaluated in another way than its operator does
-    const int e = P->precision == FMM_FP64 ? precompute_typed<double>(P, set) : precompute_typed<float>(P, set);
-    if (e) return e;
+    set_error("internal: the setup built no operators of this set");
+    return FMM_EINVAL;
   }
   const int maxl = P->dt.maxlevel;
   const int ld = P->ld;
@@ -1624,8 +1623,7 @@ extern "C" {
 
 const char *fmm_last_error(void) { return g_err.c_str(); }
 
-// products: the plan of a boundary-element operator (monopole + dipole
-// evaluations only, unless the caller takes it out by bem_fmm_plan).
+// products: the plan of a boundary-element operator (op_set).
 static int setup_common(const double *xyz_dev, const std::vector<int64_t> &off, int kernel, double kappa, int p,
                         int ncrit, int precision, fmm_stream_t stream, fmm_plan **out, bool products = false) {
   auto t0 = std::chrono::steady_clock::now();
@@ -1651,6 +1649,7 @@ static int setup_common(const double *xyz_dev, const std::vector<int64_t> &off, 
     std::lock_guard<std::mutex> lock(g_tune_mu);
     P->tune = g_tune;
   }
+  P->products = products;
   P->n = n;
   P->mol_off = off;
   P->nsurf = 6 * (p - 1) * (p - 1) + 2;
@@ -1759,7 +1758,7 @@ static int setup_common(const double *xyz_dev, const std::vector<int64_t> &off, 
     lap(3);
     }
     P->tree_hash = tree_fingerprint(P);
-    const int sets = 1 << op_set(P, true) | (products ? 0 : 1 << op_set(P, false));
+    const int sets = 1 << op_set(P, true) | 1 << op_set(P, false);
     if (fmm_plan *A = find_ops(P, sets)) {
       // a live plan of the same kernel, kappa, order and working type on the
       // same tree: its operators (they do not depend on the leaf items)
@@ -1925,7 +1924,7 @@ int fmm_info(const fmm_plan *P, fmm_info_t *o) {
     FMM_HIP_TRY(hipMemcpy(&e, P->chain_ctr + P->chain_ctr_n - 1, sizeof(e), hipMemcpyDeviceToHost));
     o->chain_timeouts = e;
   }
-  const OpSet &O = P->ops[P->ops[op_set(P, false)].built ? op_set(P, false) : 1];
+  const OpSet &O = P->ops[op_set(P, false)];
   for (int r : O.rank_u) o->rank_up = std::max(o->rank_up, (int32_t)r);
   for (int r : O.rank_d) o->rank_down = std::max(o->rank_down, (int32_t)r);
   return FMM_OK;

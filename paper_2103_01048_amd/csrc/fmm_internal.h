@@ -51,8 +51,10 @@ int tsvd_split(int rows, int cols, const double *A, double tau, double *L, int l
 // precision, the two kinds of evaluation whose results are handed on in
 // double precision (`keeps_order`): one column of one plan (the gradients of
 // autograd.py) and monopole + dipole sources (the boundary-element products).
-// Those keep their order of summation and with it every bit.  Single
-// precision takes set 1 for a few columns too (fewer than M2L_FEW_COLUMNS):
+// Those keep their order of summation and with it every bit.  The plans of a
+// boundary-element operator take set 1 for every evaluation: one that a caller
+// takes out by bem_fmm_plan finds the operators that its setup built, and no
+// evaluation builds operators.  Single precision takes set 1 for a few columns too (fewer than M2L_FEW_COLUMNS):
 // its launch spreads V pairs over the chip where the segmented one walks up to
 // eight segments in a few workgroups (600 points: 18.5 against 26.6 us).
 inline int op_set(const fmm_plan *P, bool keeps_order);
@@ -181,6 +183,9 @@ struct Chain {
 // one M2L operator serves every reflection of its offset and the segmented
 // M2L applies it.  Set 1 takes them as the SVD leaves them, with one M2L
 // operator per offset (or its two factors), for the pairwise M2L.
+// A plan's sets are built or taken from another plan during its setup, are the
+// plan's `ops_mem`'s and never change afterwards: other threads' setups read
+// them, and plans that took them outlive the plan that built them.
 struct OpSet {
   bool built = false;
   void *pool1 = nullptr;           // swizzled ld x ld matrices
@@ -340,6 +345,7 @@ struct fmm_plan {
   double setup_ms = 0;
   double setup_split[5] = {0, 0, 0, 0, 0};  // sort, tree, lists, items, operators (ms)
   int tree_on_device = 0, tree_shared = 0;
+  int products = 0;                 // a boundary-element operator's plan
   fmm_tuning_t tune{32, 16, 512, 16384, 1.15, 0, 0, 4, 0, 512, 0, 64, 0, 0, 1024, 0, 0};  // tunables in force at setup
   std::vector<void *> allocs;      // everything to free
   std::shared_ptr<fmm::SharedAllocs> tree_mem;  // the tree's device buffers (shared with plans on the same points)
@@ -351,7 +357,7 @@ struct fmm_plan {
 namespace fmm {
 inline int op_set(const fmm_plan *P, bool keeps_order) {
   return P->tune.m2l_factored ||
-                 (P->precision != FMM_FP64 && (keeps_order || P->dt.nvcol < M2L_FEW_COLUMNS))
+                 (P->precision != FMM_FP64 && (P->products || keeps_order || P->dt.nvcol < M2L_FEW_COLUMNS))
              ? 1
              : 0;
 }

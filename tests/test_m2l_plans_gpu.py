@@ -57,3 +57,63 @@ def test_pair_after_one_plan_met_more_columns(precision, first, cols):
     want = _pair(_plans(xt, precision), q[1:3])
     for got, ref in zip(_pair(plans, q[1:3]), want):
         assert torch.equal(got, ref)
+
+
+def _operator(precision, level=4):
+    from paper_2103_01048_amd import BEMOperator
+    v, t = synth.octa_sphere(level, 4.0)
+    return BEMOperator(v, t, quad_pts=3, kappa=KAPPA, p=6, ncrit=32, precision=precision)
+
+
+class _OperatorPlans:
+    """The operator's two plans (bem_fmm_plan) as FMMPlans that do not own
+    their handles."""
+
+    def __init__(self, torch, op):
+        import ctypes
+        from paper_2103_01048_amd import FMMPlan, _lib
+        self.plans = []
+        for name, kernel in (("laplace", _lib.FMM_LAPLACE), ("yukawa", _lib.FMM_YUKAWA)):
+            pl = FMMPlan.__new__(FMMPlan)
+            pl._h = ctypes.c_void_p(_lib.lib().bem_fmm_plan(op._h, kernel))
+            pl.kernel, pl.device = name, op.device
+            pl.dtype = torch.float64 if op.precision == "fp64" else torch.float32
+            pl.n = pl.info()["n_points"]
+            self.plans.append(pl)
+
+    def __enter__(self):
+        return self.plans
+
+    def __exit__(self, *a):
+        for pl in self.plans:
+            pl._h = None
+
+
+@pytest.mark.parametrize("precision", ["bf16x3", "fp32", "fp64"])
+def test_operator_plans_evaluated_after_the_operator_they_took_from_is_gone(precision):
+    """A second operator on the same mesh takes the first one's translation
+    operators, also after the first one's plans were evaluated as a pair and
+    with several columns; freeing the first changes nothing."""
+    torch = require_gpu()
+    dt = torch.float64 if precision == "fp64" else torch.float32
+
+    def both(plans):
+        return _pair(plans, q[0]) + _pair(plans, q[1:3]) + [t.clone() for pl in plans for t in pl.eval(q)]
+
+    print(f"[m2l plans] operator {precision}", flush=True)
+    op = _operator(precision)
+    with _OperatorPlans(torch, op) as plans:
+        assert _m2l_columns(plans[0]) >= 1024
+        q = torch.tensor(np.random.default_rng(163).standard_normal((4, plans[0].n)), device="cuda", dtype=dt)
+        want = both(plans)
+    op2 = _operator(precision)
+    with _OperatorPlans(torch, op2) as plans:
+        first = both(plans)
+    del op
+    torch.cuda.synchronize()
+    junk = torch.full((1 << 26,), float("nan"), device="cuda")  # takes freed device memory
+    with _OperatorPlans(torch, op2) as plans:
+        again = both(plans)
+    del junk
+    for a, b, c in zip(want, first, again):
+        assert torch.equal(a, b) and torch.equal(a, c)
