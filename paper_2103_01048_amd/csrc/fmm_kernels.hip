@@ -2334,7 +2334,7 @@ int ensure_m2l(fmm_plan *P, int nr, int set);
 int ensure_work(fmm_plan *P, int nr);
 
 // Segmented M2L of the levels [l0, l1) of plan P and, when Q is given, of plan Q
-// (sharing P's tree and precision), one launch.
+// (sharing P's tree, precision and columns per task), one launch.
 template <typename T>
 static int launch_m2l(fmm_plan *P, fmm_plan *Q, int nr, int l0, int l1, hipStream_t s) {
   auto args = [&](fmm_plan *F) {
@@ -2439,15 +2439,16 @@ static int launch_m2l(fmm_plan *P, fmm_plan *Q, int nr, int l0, int l1, hipStrea
 }
 
 // M2L of plan P and, when Q is given, of plan Q (sharing P's tree and
-// precision), levels [l0, l1): one launch for the plans of one form (a
-// factored plan first maps its upward coordinates through R).
+// precision), levels [l0, l1): one launch for the plans of one form and task
+// width (a factored plan first maps its upward coordinates through R).
 template <typename T>
 static int launch_m2l_form(fmm_plan *P, fmm_plan *Q, int nr, bool keeps_order, int l0, int l1, hipStream_t s) {
   const bool pp = op_set(P, keeps_order) == 1, pq = Q && op_set(Q, keeps_order) == 1;
   int rc;
-  if (!pp || (Q && !pq)) {
-    if ((rc = launch_m2l<T>(pp ? Q : P, !pp && Q && !pq ? Q : nullptr, nr, l0, l1, s))) return rc;
-  }
+  // one launch has one task width (the tunable m2l_cols may differ)
+  const bool one = !pp && Q && !pq && P->lists[0][nr].m2lc.nt == Q->lists[0][nr].m2lc.nt;
+  if (!pp && (rc = launch_m2l<T>(P, one ? Q : nullptr, nr, l0, l1, s))) return rc;
+  if (Q && !pq && !one && (rc = launch_m2l<T>(Q, nullptr, nr, l0, l1, s))) return rc;
   auto pair_gemm = [&](fmm_plan *A, fmm_plan *B) -> int {
     auto levels = [&](fmm_plan *F) {
       const PassLists &L = F->lists[1][nr];

@@ -117,3 +117,30 @@ def test_operator_plans_evaluated_after_the_operator_they_took_from_is_gone(prec
     del junk
     for a, b, c in zip(want, first, again):
         assert torch.equal(a, b) and torch.equal(a, c)
+
+
+@pytest.mark.parametrize("widths", [(128, 64), (64, 128), (128, 128)])
+def test_pair_of_plans_set_up_under_different_m2l_cols(widths):
+    """Columns per task differ between the two plans; a column's products and
+    their order do not depend on it, so neither does a bit of the results."""
+    torch = require_gpu()
+    from paper_2103_01048_amd import FMMPlan, autotune
+    xt = torch.tensor(_cloud(9000), device="cuda")
+    q = torch.tensor(np.random.default_rng(164).standard_normal((2, len(xt))), device="cuda", dtype=torch.float32)
+
+    def plans(cols):
+        out = []
+        for kernel, c in zip(("laplace", "yukawa"), cols):
+            with autotune.tuning(**{**autotune.DEFAULTS, "m2l_cols": c}):
+                out.append(FMMPlan(xt, kernel=kernel, kappa=KAPPA, p=6, ncrit=32, precision="bf16x3"))
+        return out
+
+    print(f"[m2l plans] m2l_cols {widths}", flush=True)
+    ref = plans((64, 64))
+    # at least 160 tasks of 64 columns, so that the plans' widths are their m2l_cols
+    assert _m2l_columns(ref[0]) >= 160 * 64
+    want = [_pair(ref, q[0]), _pair(ref, q)]
+    pl = plans(widths)
+    for qq, w in zip((q[0], q), want):
+        for got, r in zip(_pair(pl, qq), w):
+            assert torch.equal(got, r)
