@@ -1320,27 +1320,44 @@ int ensure_lists(fmm_plan *P, int nr, int set) {
   return FMM_OK;
 }
 
-// Slots of the M2L form of an operator set for nr columns.
-int ensure_m2l(fmm_plan *P, int nr, int set) {
+// Buffers of every M2L form that the plan's evaluations of nr columns take
+// (op_set), one buffer for the slots of all: a plan that has evaluated nr
+// columns in one way has what it needs to do so in another, inside a graph
+// capture too, where nothing can be allocated.
+int ensure_m2l(fmm_plan *P, int nr) {
+  if ((P->m2l_ready >> nr) & 1) return FMM_OK;
   const size_t es = P->precision == FMM_FP64 ? 8 : 4;
+  const int sets = 1 << op_set(P, false) | 1 << op_set(P, nr == 1);
   int rc;
-  if (set == 1) {
-    if (P->pairbuf_nr >= nr) return FMM_OK;
-    const int64_t np = std::max<int64_t>(1, P->loff[1].back());
-    const int ldt = P->ops[1].m2l_ldt;
-    if ((rc = dev_alloc(P, &P->pairbuf, (size_t)np * nr * pair_ld(P, 1) * es))) return rc;
-    if (ldt > 0 && (rc = dev_alloc(P, &P->m2l_t, (size_t)np * nr * ldt * es))) return rc;
-    P->pairbuf_nr = nr;
+  // a buffer that is too small is replaced, never one that is in use for more columns
+  auto grow = [&](void **buf, size_t *have, size_t need) -> int {
+    if (*have >= need) return FMM_OK;
+    void *b = nullptr;
+    if (int e = dev_alloc(P, &b, need)) return e;
+    *buf = b;
+    *have = need;
     return FMM_OK;
+  };
+  size_t bytes = 16;
+  if (sets & 2) {
+    const size_t np = (size_t)P->loff[1].back() * nr;
+    const int ldt = P->ops[1].m2l_ldt;
+    bytes = std::max(bytes, np * pair_ld(P, 1) * es);
+    if ((rc = grow(&P->m2l_t, &P->m2l_t_bytes, np * ldt * es))) return rc;
   }
-  if (P->colbuf_nr >= nr) return FMM_OK;
-  if (P->precision == FMM_FP32_BF16X3) {
-    const size_t bytes = 2 * ((size_t)P->dt.nbox * nr + 1) * P->ld * 2;
-    if ((rc = dev_alloc(P, &P->cub, bytes))) return rc;
-    FMM_HIP_TRY(hipMemset(P->cub, 0, bytes));
+  if (sets & 1) {
+    bytes = std::max(bytes, (size_t)P->dt.nvcol * nr * pair_ld(P, 0) * es);
+    if (P->precision == FMM_FP32_BF16X3 && P->cub_nr < nr) {
+      const size_t cb = 2 * ((size_t)P->dt.nbox * nr + 1) * P->ld * 2;
+      void *b = nullptr;
+      if ((rc = dev_alloc(P, &b, cb))) return rc;
+      FMM_HIP_TRY(hipMemset(b, 0, cb));
+      P->cub = b;
+      P->cub_nr = nr;
+    }
   }
-  if ((rc = dev_alloc(P, &P->colbuf, (size_t)std::max<int64_t>(1, P->dt.nvcol) * nr * pair_ld(P, 0) * es))) return rc;
-  P->colbuf_nr = nr;
+  if ((rc = grow(&P->m2lbuf, &P->m2lbuf_bytes, bytes))) return rc;
+  P->m2l_ready |= 1 << nr;
   return FMM_OK;
 }
 

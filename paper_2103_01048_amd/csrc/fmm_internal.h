@@ -304,10 +304,12 @@ struct fmm_plan {
   void *surf = nullptr;            // T4 grid offsets in [-1,1]^3, nsurf entries
   fmm::OpSet ops[2];               // translation operators (OpSet)
   // work arrays, sized for work_nr columns
-  int work_nr = 0, colbuf_nr = 0, pairbuf_nr = 0;
+  int work_nr = 0, cub_nr = 0;
+  int m2l_ready = 0;               // bit nr: the M2L buffers hold nr columns
   void *qs = nullptr, *equ = nullptr, *chk = nullptr, *eqd = nullptr, *chku = nullptr,
-       *cu = nullptr, *yd = nullptr, *pairbuf = nullptr, *colbuf = nullptr, *cub = nullptr, *mslot = nullptr, *m2l_t = nullptr;
-  // cub: cu split into bf16 high and low parts (bf16x3, segmented M2L)
+       *cu = nullptr, *yd = nullptr, *m2lbuf = nullptr, *cub = nullptr, *mslot = nullptr, *m2l_t = nullptr;
+  // m2lbuf: M2L slots, one per V pair (pairwise) or per column (segmented)
+  // cub: cu split into bf16 high and low parts (bf16x3, segmented M2L), for cub_nr columns
   // cu: upward check in singular coordinates (U_u^T chk); yd: downward
   // check in singular coordinates (M2L sums + U_d^T chk)
   void *ydx[fmm::MAX_NR + 1] = {};  // P2L projections, by the number of columns
@@ -328,6 +330,7 @@ struct fmm_plan {
   hipStream_t aux = nullptr, aux2 = nullptr, aux3 = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_up = nullptr, ev_m2l = nullptr, ev_near = nullptr;
   hipEvent_t ev_m2m = nullptr, ev_m2lf = nullptr;  // the first M2M level done; the early M2L levels done
+  size_t m2lbuf_bytes = 0, m2l_t_bytes = 0;
   void *pair_acc = nullptr;
   size_t pair_acc_bytes = 0;
   void *dips = nullptr;             // monopole + dipole sources: dipole records in Morton order

@@ -2330,7 +2330,7 @@ static int launch_gemm(fmm_plan *P, const GemmBatch &bt, const T *X, T *Y, hipSt
 }
 
 int ensure_lists(fmm_plan *P, int nr, int set);   // host planner
-int ensure_m2l(fmm_plan *P, int nr, int set);
+int ensure_m2l(fmm_plan *P, int nr);
 int ensure_work(fmm_plan *P, int nr);
 
 // Segmented M2L of the levels [l0, l1) of plan P and, when Q is given, of plan Q
@@ -2355,9 +2355,9 @@ static int launch_m2l(fmm_plan *P, fmm_plan *Q, int nr, int l0, int l1, hipStrea
     g.mstride = bf3 ? (int64_t)(F->ld / 16) * O.bf_kb * 2 * 64 : (int64_t)F->ld * F->ld;
     g.X = bf3 ? F->cub : F->cu;
     // the row past the buffer's last box is never written
-    g.zrow = F->dt.nbox * (bf3 ? F->colbuf_nr : F->work_nr);
+    g.zrow = F->dt.nbox * (bf3 ? F->cub_nr : F->work_nr);
     g.xlo = ((int64_t)g.zrow + 1) * F->ld;
-    g.Y = F->colbuf;
+    g.Y = F->m2lbuf;
     g.nrb = L.m2lc.nrb;
     g.nrbk = L.m2lc.nrbk;
     g.ldx = F->ld;
@@ -2466,8 +2466,8 @@ static int launch_m2l_form(fmm_plan *P, fmm_plan *Q, int nr, bool keeps_order, i
                               B ? (T *)B->m2l_t : nullptr, s);
       if (r) return r;
     }
-    return launch_gemm2<T>(A, ba, (const T *)(f ? A->m2l_t : A->cu), (T *)A->pairbuf, B, &bb,
-                           B ? (const T *)(f ? B->m2l_t : B->cu) : nullptr, B ? (T *)B->pairbuf : nullptr, s);
+    return launch_gemm2<T>(A, ba, (const T *)(f ? A->m2l_t : A->cu), (T *)A->m2lbuf, B, &bb,
+                           B ? (const T *)(f ? B->m2l_t : B->cu) : nullptr, B ? (T *)B->m2lbuf : nullptr, s);
   };
   if (pp && pq && (P->tune.m2l_factored != 0) == (Q->tune.m2l_factored != 0)) return pair_gemm(P, Q);
   if (pp && (rc = pair_gemm(P, nullptr))) return rc;
@@ -2484,7 +2484,7 @@ static int launch_m2l_sum(fmm_plan *P, fmm_plan *Q, int nr, bool keeps_order, hi
   auto go = [&](fmm_plan *A, fmm_plan *B, bool pw) {
     auto ldp = [&](fmm_plan *F) { return pw ? F->lists[1][nr].m2l.ldy : F->lists[0][nr].m2lc.ldy; };
     auto rows = [&](fmm_plan *F) { return 16 * (pw ? F->lists[1][nr].m2l.nrb : F->lists[0][nr].m2lc.nrb); };
-    auto slots = [&](fmm_plan *F) { return (const T *)(pw ? F->pairbuf : F->colbuf); };
+    auto slots = [](fmm_plan *F) { return (const T *)F->m2lbuf; };
     hipLaunchKernelGGL(k_pair_reduce<T>, dim3(D.nvbox, B ? 2 : 1), dim3(64), 0, s, D.v_tgt,
                        pw ? A->d_vp_off : D.v_off, pw ? A->d_vp_pair : D.v_pair, slots(A), (T *)A->yd, nr, A->ld,
                        ldp(A), rows(A), B ? slots(B) : nullptr, B ? (T *)B->yd : nullptr, B ? ldp(B) : 0,
@@ -2903,7 +2903,7 @@ static int eval_typed(fmm_plan *P, const T *q, int nrhs, T *pot, T *grad, hipStr
     int rc;
     if ((rc = ensure_work(P, nr))) return rc;
     if ((rc = ensure_lists(P, nr, op_set(P, nr == 1)))) return rc;
-    if ((rc = ensure_m2l(P, nr, op_set(P, nr == 1)))) return rc;
+    if ((rc = ensure_m2l(P, nr))) return rc;
     const T *qc = q + (int64_t)c0 * N;
     T *pc = pot + (int64_t)c0 * N;
     T *gc = grad ? grad + (int64_t)c0 * N * 3 : nullptr;
@@ -3100,7 +3100,8 @@ static int eval_pair_typed(fmm_plan *A, fmm_plan *B, const T *q, int nrhs, T *po
     int rc;
     const int sa = op_set(A, false), sb = op_set(B, false);
     if ((rc = ensure_work(A, nr)) || (rc = ensure_lists(A, nr, sa)) || (rc = ensure_work(B, nr)) ||
-        (rc = ensure_lists(B, nr, sb)) || (rc = ensure_m2l(A, nr, sa)) || (rc = ensure_m2l(B, nr, sb)) || (rc = ensure_pair(A, B, nr)))
+        (rc = ensure_lists(B, nr, sb)) || (rc = ensure_m2l(A, nr)) || (rc = ensure_m2l(B, nr)) ||
+        (rc = ensure_pair(A, B, nr)))
       return rc;
     const T *qc = q + (int64_t)c0 * N;
     T *pa = pot_a + (int64_t)c0 * N, *pb = pot_b + (int64_t)c0 * N;
@@ -3137,7 +3138,8 @@ static int eval_pair_md_typed(fmm_plan *A, fmm_plan *B, const T *q, const T *dip
   int rc;
   const int sa = op_set(A, true), sb = op_set(B, true);
   if ((rc = ensure_work(A, 1)) || (rc = ensure_lists(A, 1, sa)) || (rc = ensure_work(B, 1)) ||
-      (rc = ensure_lists(B, 1, sb)) || (rc = ensure_m2l(A, 1, sa)) || (rc = ensure_m2l(B, 1, sb)) || (rc = ensure_pair(A, B, 1)) || (rc = ensure_pair_md(A, B)))
+      (rc = ensure_lists(B, 1, sb)) || (rc = ensure_m2l(A, 1)) || (rc = ensure_m2l(B, 1)) ||
+      (rc = ensure_pair(A, B, 1)) || (rc = ensure_pair_md(A, B)))
     return rc;
   const DevTree &D = A->dt;
   const int64_t N = A->n;

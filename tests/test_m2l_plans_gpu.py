@@ -144,3 +144,66 @@ def test_pair_of_plans_set_up_under_different_m2l_cols(widths):
     for qq, w in zip((q[0], q), want):
         for got, r in zip(_pair(pl, qq), w):
             assert torch.equal(got, r)
+
+
+def _replay_equals_eager(torch, warm, fn):
+    """fn captured after `warm` ran eagerly and before fn itself ever did;
+    three replays with eager work between them against the eager result."""
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        warm()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        out = fn()
+    want = [t.clone() for t in fn()]
+    for _ in range(3):
+        for t in out:
+            t.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, want))
+        warm()
+        torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("precision", ["bf16x3", "fp32", "fp64"])
+@pytest.mark.parametrize("form", ["single after pair", "pair after products", "single after five columns"])
+def test_one_column_captured_after_another_form_of_evaluation(precision, form):
+    """A plan that has evaluated one column in one way evaluates one in
+    another inside a graph capture, where nothing can be allocated."""
+    torch = require_gpu()
+    from paper_2103_01048_amd import eval_pair
+    from paper_2103_01048_amd.fmm import eval_pair_md
+    xt = torch.tensor(_cloud(), device="cuda")
+    dt = torch.float64 if precision == "fp64" else torch.float32
+    rng = np.random.default_rng(165)
+    q = torch.tensor(rng.standard_normal((5, len(xt))), device="cuda", dtype=dt)
+    dip = torch.tensor(rng.standard_normal((len(xt), 3)), device="cuda", dtype=dt)
+    a, b = _plans(xt, precision)
+    assert _m2l_columns(a) >= 1024
+    print(f"[m2l plans] capture {precision} {form}", flush=True)
+    if form == "single after pair":
+        _replay_equals_eager(torch, lambda: eval_pair(a, b, q[0]), lambda: list(b.eval(q[1])))
+    elif form == "pair after products":
+        _replay_equals_eager(torch, lambda: eval_pair_md(a, b, q[0], dip),
+                             lambda: [t for o in eval_pair(a, b, q[1]) for t in o])
+    else:
+        _replay_equals_eager(torch, lambda: eval_pair(a, b, q), lambda: list(a.eval(q[1])))
+
+
+@pytest.mark.parametrize("precision", ["bf16x3", "fp32"])
+def test_factored_m2l_buffers_after_fewer_columns(precision):
+    """Four columns, then one, then four again: the buffers of the four stay."""
+    torch = require_gpu()
+    from paper_2103_01048_amd import autotune
+    xt = torch.tensor(_cloud(700), device="cuda")
+    q = torch.tensor(np.random.default_rng(166).standard_normal((4, len(xt))), device="cuda", dtype=torch.float32)
+    with autotune.tuning(**{**autotune.DEFAULTS, "m2l_factored": 1}):
+        plans = _plans(xt, precision)
+    print(f"[m2l plans] factored {precision}", flush=True)
+    four, one = _pair(plans, q), _pair(plans, q[0])
+    for got, want in ((_pair(plans, q), four), (_pair(plans, q[0]), one)):
+        assert all(torch.equal(u, w) for u, w in zip(got, want))
