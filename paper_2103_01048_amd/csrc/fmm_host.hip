@@ -1566,29 +1566,36 @@ static fmm_plan *find_tree(const fmm_plan *P) {
   return nullptr;
 }
 
-// A live plan whose translation operators P can take: the same kernel,
-// kappa, order and working type on a tree of the same points, root cube and
-// ncrit (the operators depend on the level sizes and on the offsets the V
-// lists use, not on the leaf items).
-static fmm_plan *find_ops(const fmm_plan *P, int sets) {
-  std::lock_guard<std::mutex> lock(g_tree_mu);
-  for (fmm_plan *A : g_tree_plans)
-    if (A->ops_mem && !(sets & ~(A->ops[0].built | A->ops[1].built << 1)) && A->kernel == P->kernel && A->kappa == P->kappa && A->p == P->p &&
-        A->tune.m2l_factored == P->tune.m2l_factored &&
-        A->precision == P->precision && A->coord_hash == P->coord_hash && A->n == P->n &&
-        A->mol_off == P->mol_off && A->W == P->W && A->mol_lo == P->mol_lo && A->ncrit == P->ncrit &&
-        A->device == P->device && A->level_begin == P->level_begin && A->loff[1] == P->loff[1] &&
-        A->lidx[1] == P->lidx[1])
-      return A;
-  return nullptr;
+// Whether P can take A's translation operators: the same kernel, kappa, order
+// and working type on a tree of the same points, root cube and ncrit (the
+// operators depend on the level sizes and on the offsets the V lists use, not
+// on the leaf items).
+static bool same_operators(const fmm_plan *A, const fmm_plan *P) {
+  return A->kernel == P->kernel && A->kappa == P->kappa && A->p == P->p &&
+         A->tune.m2l_factored == P->tune.m2l_factored && A->precision == P->precision &&
+         A->coord_hash == P->coord_hash && A->n == P->n && A->mol_off == P->mol_off && A->W == P->W &&
+         A->mol_lo == P->mol_lo && A->ncrit == P->ncrit && A->device == P->device &&
+         A->level_begin == P->level_begin && A->loff[1] == P->loff[1] && A->lidx[1] == P->lidx[1];
 }
 
-static void share_ops(fmm_plan *P, const fmm_plan *A) {
-  P->ops_mem = A->ops_mem;
-  for (int k = 0; k < 2; ++k) P->ops[k] = A->ops[k];
-  P->surf = A->surf;
-  P->dt.box_geom = A->dt.box_geom;
-  P->ops_shared = 1;
+// P takes the operator sets among `sets` (bit k: set k) that live plans have,
+// each from any of them, and the surface grid and box geometry.  A plan in the
+// list is whole while the lock is held: it is entered after its setup and
+// leaves before it is freed.
+static void take_ops(fmm_plan *P, int sets) {
+  std::lock_guard<std::mutex> lock(g_tree_mu);
+  for (const fmm_plan *A : g_tree_plans) {
+    bool want = !P->geom_mem && A->geom_mem;
+    for (int k = 0; k < 2; ++k) want |= ((sets >> k) & 1) && !P->ops[k].built && A->ops[k].built;
+    if (!want || !same_operators(A, P)) continue;
+    for (int k = 0; k < 2; ++k)
+      if (((sets >> k) & 1) && !P->ops[k].built) P->ops[k] = A->ops[k];
+    if (!P->geom_mem) {
+      P->geom_mem = A->geom_mem;
+      P->surf = A->surf;
+      P->dt.box_geom = A->dt.box_geom;
+    }
+  }
 }
 
 static void register_tree(fmm_plan *P) {
@@ -1776,20 +1783,22 @@ static int setup_common(const double *xyz_dev, const std::vector<int64_t> &off, 
     }
     P->tree_hash = tree_fingerprint(P);
     const int sets = 1 << op_set(P, true) | 1 << op_set(P, false);
-    if (fmm_plan *A = find_ops(P, sets)) {
-      // a live plan of the same kernel, kappa, order and working type on the
-      // same tree: its operators (they do not depend on the leaf items)
-      share_ops(P, A);
-    } else {
-      P->ops_mem = std::make_shared<SharedAllocs>();
-      P->alloc_sink = &P->ops_mem->ptrs;
-      // the sets that the plan's evaluations take
-      for (int set = 0; set < 2 && !rc; ++set)
-        if ((sets >> set) & 1) rc = precision == FMM_FP64 ? precompute_typed<double>(P, set) : precompute_typed<float>(P, set);
-      if (!rc) rc = precision == FMM_FP64 ? upload_geometry<double>(P) : upload_geometry<float>(P);
-      P->alloc_sink = nullptr;
-      if (rc) break;
+    // the sets that the plan's evaluations take: those of live plans, the
+    // others built
+    take_ops(P, sets);
+    for (int set = 0; set < 2 && !rc; ++set) {
+      if (!((sets >> set) & 1) || P->ops[set].built) continue;
+      P->ops[set].mem = std::make_shared<SharedAllocs>();
+      P->alloc_sink = &P->ops[set].mem->ptrs;
+      rc = precision == FMM_FP64 ? precompute_typed<double>(P, set) : precompute_typed<float>(P, set);
     }
+    if (!rc && !P->geom_mem) {
+      P->geom_mem = std::make_shared<SharedAllocs>();
+      P->alloc_sink = &P->geom_mem->ptrs;
+      rc = precision == FMM_FP64 ? upload_geometry<double>(P) : upload_geometry<float>(P);
+    }
+    P->alloc_sink = nullptr;
+    if (rc) break;
     // the task lists of one-column evaluations
     for (int set = 0; set < 2 && !rc; ++set)
       if ((sets >> set) & 1) rc = ensure_lists(P, 1, set);

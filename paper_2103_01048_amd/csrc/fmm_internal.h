@@ -178,16 +178,27 @@ struct Chain {
   void *tasks = nullptr, *gargs = nullptr, *rargs = nullptr, *need = nullptr;
 };
 
+// Device buffers that plans on the same points share (a tree's sorted order,
+// boxes, lists and leaf items; a set of operators; the surface grid); freed
+// when the last plan holding them is.
+struct SharedAllocs {
+  std::vector<void *> ptrs;
+  ~SharedAllocs() {
+    for (void *p : ptrs) (void)hipFree(p);
+  }
+};
+
 // Translation operators of a plan in one basis of singular coordinates.  Set 0
 // takes singular vectors of one reflection class each (tsvd_factors_parity):
 // one M2L operator serves every reflection of its offset and the segmented
 // M2L applies it.  Set 1 takes them as the SVD leaves them, with one M2L
 // operator per offset (or its two factors), for the pairwise M2L.
-// A plan's sets are built or taken from another plan during its setup, are the
-// plan's `ops_mem`'s and never change afterwards: other threads' setups read
-// them, and plans that took them outlive the plan that built them.
+// A plan's sets are built or taken from another plan during its setup and
+// never change afterwards: other threads' setups read them, and plans that
+// took them outlive the plan that built them.
 struct OpSet {
   bool built = false;
+  std::shared_ptr<SharedAllocs> mem;  // its device buffers
   void *pool1 = nullptr;           // swizzled ld x ld matrices
   int64_t pool1_count = 0, poolbf_count = 0;
   void *pool_bf = nullptr;         // bf16x3 mode: split M2L operators
@@ -259,15 +270,6 @@ struct DevTree {
   // per level: non-leaf boxes, CSR of their children (for the M2M sums)
   std::vector<int32_t *> m2m_tgt, m2m_off, m2m_kid;
   std::vector<int> m2m_n;
-};
-
-// Device buffers of a tree (sorted order, boxes, lists, leaf items) that
-// plans on the same points share; freed when the last plan holding them is.
-struct SharedAllocs {
-  std::vector<void *> ptrs;
-  ~SharedAllocs() {
-    for (void *p : ptrs) (void)hipFree(p);
-  }
 };
 
 }  // namespace fmm
@@ -352,8 +354,7 @@ struct fmm_plan {
   fmm_tuning_t tune{32, 16, 512, 16384, 1.15, 0, 0, 4, 0, 512, 0, 64, 0, 0, 1024, 0, 0};  // tunables in force at setup
   std::vector<void *> allocs;      // everything to free
   std::shared_ptr<fmm::SharedAllocs> tree_mem;  // the tree's device buffers (shared with plans on the same points)
-  std::shared_ptr<fmm::SharedAllocs> ops_mem;   // translation operators (shared with plans of the same kernel on the same tree)
-  int ops_shared = 0;
+  std::shared_ptr<fmm::SharedAllocs> geom_mem;  // surface grid and box geometry (shared with plans of the same kernel on the same tree)
   std::vector<void *> *alloc_sink = nullptr;    // where dev_alloc records a buffer (null: allocs)
 };
 

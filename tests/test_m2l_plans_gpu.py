@@ -207,3 +207,40 @@ def test_factored_m2l_buffers_after_fewer_columns(precision):
     four, one = _pair(plans, q), _pair(plans, q[0])
     for got, want in ((_pair(plans, q), four), (_pair(plans, q[0]), one)):
         assert all(torch.equal(u, w) for u, w in zip(got, want))
+
+
+@pytest.mark.parametrize("precision", ["bf16x3", "fp32", "fp64"])
+def test_plan_takes_the_operators_that_a_live_operator_has(precision):
+    """A plan on a live operator's quadrature points builds only the operators
+    that the operator does not hold, keeps what it took when the operator is
+    freed, and gives the same results to the bit as one that built them all."""
+    torch = require_gpu()
+    v, t = synth.octa_sphere(4, 4.0)
+    l1, l2 = np.array([1 / 6, 2 / 3, 1 / 6])[None, :, None], np.array([1 / 6, 1 / 6, 2 / 3])[None, :, None]
+    tri = v[t][:, None]
+    x = torch.tensor(((1 - l1 - l2) * tri[:, :, 0] + l1 * tri[:, :, 1] + l2 * tri[:, :, 2]).reshape(-1, 3), device="cuda")
+    dt = torch.float64 if precision == "fp64" else torch.float32
+    q = torch.tensor(np.random.default_rng(167).standard_normal((2, len(x))), device="cuda", dtype=dt)
+
+    def results(plans):
+        return _pair(plans, q[0]) + [u.clone() for pl in plans for u in pl.eval(q[0]) + pl.eval(q)]
+
+    print(f"[m2l plans] operators of an operator {precision}", flush=True)
+    alone = _plans(x, precision)
+    inf = alone[0].info()
+    bytes_alone, ns, want = inf["device_bytes"], inf["n_surf"], results(alone)
+    del alone
+    op = _operator(precision)
+    plans = _plans(x, precision)
+    inf = plans[0].info()
+    assert inf["tree_shared"] == 1
+    # what it took holds n_surf x n_surf M2L operators: the segmented form's 56 at most per level in
+    # FP64, the pairwise form's 316 at most in single precision (this surface uses most of them)
+    taken = 50 * 8 * ns * ns if precision == "fp64" else 200 * 4 * ns * ns
+    assert bytes_alone - inf["device_bytes"] > taken
+    del op
+    torch.cuda.synchronize()
+    junk = torch.full((1 << 26,), float("nan"), device="cuda")
+    for a, b in zip(results(plans), want):
+        assert torch.equal(a, b)
+    del junk
