@@ -1320,45 +1320,42 @@ int ensure_lists(fmm_plan *P, int nr, int set) {
   return FMM_OK;
 }
 
-// Buffers of every M2L form that the plan's evaluations of nr columns take
-// (op_set), one buffer for the slots of all: a plan that has evaluated nr
-// columns in one way has what it needs to do so in another, inside a graph
-// capture too, where nothing can be allocated.
-int ensure_m2l(fmm_plan *P, int nr) {
-  if ((P->m2l_ready >> nr) & 1) return FMM_OK;
-  const size_t es = P->precision == FMM_FP64 ? 8 : 4;
-  const int sets = 1 << op_set(P, false) | 1 << op_set(P, nr == 1);
-  int rc;
-  // a buffer that is too small is replaced, never one that is in use for more columns
-  auto grow = [&](void **buf, size_t *have, size_t need) -> int {
-    if (*have >= need) return FMM_OK;
-    void *b = nullptr;
-    if (int e = dev_alloc(P, &b, need)) return e;
-    *buf = b;
-    *have = need;
-    return FMM_OK;
-  };
-  size_t bytes = 16;
-  if (sets & 2) {
-    const size_t np = (size_t)P->loff[1].back() * nr;
-    const int ldt = P->ops[1].m2l_ldt;
-    bytes = std::max(bytes, np * pair_ld(P, 1) * es);
-    if ((rc = grow(&P->m2l_t, &P->m2l_t_bytes, np * ldt * es))) return rc;
-  }
-  if (sets & 1) {
-    bytes = std::max(bytes, (size_t)P->dt.nvcol * nr * pair_ld(P, 0) * es);
-    if (P->precision == FMM_FP32_BF16X3 && P->cub_nr < nr) {
-      const size_t cb = 2 * ((size_t)P->dt.nbox * nr + 1) * P->ld * 2;
-      void *b = nullptr;
-      if ((rc = dev_alloc(P, &b, cb))) return rc;
-      FMM_HIP_TRY(hipMemset(b, 0, cb));
-      P->cub = b;
-      P->cub_nr = nr;
-    }
-  }
-  if ((rc = grow(&P->m2lbuf, &P->m2lbuf_bytes, bytes))) return rc;
-  P->m2l_ready |= 1 << nr;
+// A buffer of at least `need` bytes; one that is too small is replaced (and
+// freed with the plan).  Allocated inside a graph capture too: a plan that has
+// evaluated nr columns in one way may be captured doing so in another.
+static int grow(fmm_plan *P, void **buf, size_t *have, size_t need) {
+  if (*have >= need && *buf) return FMM_OK;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  FMM_HIP_TRY(hipThreadExchangeStreamCaptureMode(&mode));
+  void *b = nullptr;
+  const int rc = dev_alloc(P, &b, need);
+  FMM_HIP_TRY(hipThreadExchangeStreamCaptureMode(&mode));
+  if (rc) return rc;
+  *buf = b;
+  *have = need;
   return FMM_OK;
+}
+
+// Buffers of the M2L of nr columns in the form of an operator set.  The slots
+// of both forms share one buffer.  The buffer of the split columns is made for
+// the pairwise form's evaluations as well (it has to be cleared, which a graph
+// capture would record).
+int ensure_m2l(fmm_plan *P, int nr, int set) {
+  const size_t es = P->precision == FMM_FP64 ? 8 : 4;
+  int rc;
+  if (P->precision == FMM_FP32_BF16X3 && op_set(P, false) == 0 && P->cub_nr < nr) {
+    const size_t bytes = 2 * ((size_t)P->dt.nbox * nr + 1) * P->ld * 2;
+    void *b = nullptr;
+    if ((rc = dev_alloc(P, &b, bytes))) return rc;
+    FMM_HIP_TRY(hipMemset(b, 0, bytes));
+    P->cub = b;
+    P->cub_nr = nr;
+  }
+  const size_t np = (size_t)P->loff[1].back() * nr;
+  const int ldt = set == 1 ? P->ops[1].m2l_ldt : 0;
+  if (ldt > 0 && (rc = grow(P, &P->m2l_t, &P->m2l_t_bytes, np * ldt * es))) return rc;
+  const size_t slots = set == 1 ? np : (size_t)P->dt.nvcol * nr;
+  return grow(P, &P->m2lbuf, &P->m2lbuf_bytes, slots * pair_ld(P, set) * es);
 }
 
 // FNV-1a over everything the shared launches of a pair evaluation depend on:

@@ -307,7 +307,6 @@ struct fmm_plan {
   fmm::OpSet ops[2];               // translation operators (OpSet)
   // work arrays, sized for work_nr columns
   int work_nr = 0, cub_nr = 0;
-  int m2l_ready = 0;               // bit nr: the M2L buffers hold nr columns
   void *qs = nullptr, *equ = nullptr, *chk = nullptr, *eqd = nullptr, *chku = nullptr,
        *cu = nullptr, *yd = nullptr, *m2lbuf = nullptr, *cub = nullptr, *mslot = nullptr, *m2l_t = nullptr;
   // m2lbuf: M2L slots, one per V pair (pairwise) or per column (segmented)

@@ -2330,7 +2330,7 @@ static int launch_gemm(fmm_plan *P, const GemmBatch &bt, const T *X, T *Y, hipSt
 }
 
 int ensure_lists(fmm_plan *P, int nr, int set);   // host planner
-int ensure_m2l(fmm_plan *P, int nr);
+int ensure_m2l(fmm_plan *P, int nr, int set);
 int ensure_work(fmm_plan *P, int nr);
 
 // Segmented M2L of the levels [l0, l1) of plan P and, when Q is given, of plan Q
@@ -2903,7 +2903,7 @@ static int eval_typed(fmm_plan *P, const T *q, int nrhs, T *pot, T *grad, hipStr
     int rc;
     if ((rc = ensure_work(P, nr))) return rc;
     if ((rc = ensure_lists(P, nr, op_set(P, nr == 1)))) return rc;
-    if ((rc = ensure_m2l(P, nr))) return rc;
+    if ((rc = ensure_m2l(P, nr, op_set(P, nr == 1)))) return rc;
     const T *qc = q + (int64_t)c0 * N;
     T *pc = pot + (int64_t)c0 * N;
     T *gc = grad ? grad + (int64_t)c0 * N * 3 : nullptr;
@@ -3100,7 +3100,7 @@ static int eval_pair_typed(fmm_plan *A, fmm_plan *B, const T *q, int nrhs, T *po
     int rc;
     const int sa = op_set(A, false), sb = op_set(B, false);
     if ((rc = ensure_work(A, nr)) || (rc = ensure_lists(A, nr, sa)) || (rc = ensure_work(B, nr)) ||
-        (rc = ensure_lists(B, nr, sb)) || (rc = ensure_m2l(A, nr)) || (rc = ensure_m2l(B, nr)) ||
+        (rc = ensure_lists(B, nr, sb)) || (rc = ensure_m2l(A, nr, sa)) || (rc = ensure_m2l(B, nr, sb)) ||
         (rc = ensure_pair(A, B, nr)))
       return rc;
     const T *qc = q + (int64_t)c0 * N;
@@ -3138,7 +3138,7 @@ static int eval_pair_md_typed(fmm_plan *A, fmm_plan *B, const T *q, const T *dip
   int rc;
   const int sa = op_set(A, true), sb = op_set(B, true);
   if ((rc = ensure_work(A, 1)) || (rc = ensure_lists(A, 1, sa)) || (rc = ensure_work(B, 1)) ||
-      (rc = ensure_lists(B, 1, sb)) || (rc = ensure_m2l(A, 1)) || (rc = ensure_m2l(B, 1)) ||
+      (rc = ensure_lists(B, 1, sb)) || (rc = ensure_m2l(A, 1, sa)) || (rc = ensure_m2l(B, 1, sb)) ||
       (rc = ensure_pair(A, B, 1)) || (rc = ensure_pair_md(A, B)))
     return rc;
   const DevTree &D = A->dt;
