@@ -26,6 +26,7 @@
 #include <atomic>
 #include <array>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <thread>
 
@@ -267,6 +268,12 @@ static void parallel_for(int64_t count, F f) {
   for (auto &t : th) t.join();
 }
 
+// f(begin, end) over [0, n) in ranges of `grain`; one range runs here.
+template <typename F>
+static void parallel_ranges(int64_t n, int64_t grain, F f) {
+  parallel_for((n + grain - 1) / grain, [&](int64_t i) { f(i * grain, std::min(n, (i + 1) * grain)); });
+}
+
 // Swizzle a dense row-major matrix A (rows x K, lda) into the MFMA fragment
 // order used by k_gemm: element [((rb*(K/16) + kq)*64 + lane)*4 + t] holds
 // A[rb*16 + slot(lane%16)][(kq*4 + t)*4 + lane/16].
@@ -327,8 +334,28 @@ static void swizzle_bf3(const double *A, int rows, int cols, int lda, int ld_row
         }
 }
 
+// Offsets that occur in the V lists, [level][343 offset code].
+static std::vector<std::vector<char>> used_offsets(const fmm_plan *P) {
+  const int nl = (int)P->level_begin.size() - 1;
+  std::vector<std::vector<char>> used(nl, std::vector<char>(343, 0));
+  std::mutex mu;
+  parallel_ranges((int64_t)P->level.size(), 4096, [&](int64_t b0, int64_t b1) {
+    std::vector<char> mine((size_t)nl * 343, 0);
+    for (int64_t b = b0; b < b1; ++b)
+      for (int64_t k = P->loff[1][b]; k < P->loff[1][b + 1]; ++k) {
+        const int64_t a = P->lidx[1][k];
+        mine[P->level[b] * 343 + m2l_code((int)(P->anchor[3 * a] - P->anchor[3 * b]),
+                                          (int)(P->anchor[3 * a + 1] - P->anchor[3 * b + 1]),
+                                          (int)(P->anchor[3 * a + 2] - P->anchor[3 * b + 2]))] = 1;
+      }
+    std::lock_guard<std::mutex> lock(mu);
+    for (size_t i = 0; i < mine.size(); ++i) used[i / 343][i % 343] |= mine[i];
+  });
+  return used;
+}
+
 template <typename T>
-static int precompute_typed(fmm_plan *P, int set) {
+static int precompute_typed(fmm_plan *P, int set, const std::vector<std::vector<char>> &used) {
   OpSet &O = P->ops[set];
   const int p = P->p, n = P->nsurf, ld = P->ld;
   const int yuk = P->kernel == FMM_YUKAWA;
@@ -349,15 +376,10 @@ static int precompute_typed(fmm_plan *P, int set) {
   // (at most 56 instead of 316 per level).  Set 1 stores every offset.
   const bool sym = set == 0, fact = P->tune.m2l_factored && !sym;
   std::vector<std::vector<char>> m2l_used(maxl + 1, std::vector<char>(343, 0));
-  for (int64_t b = 0; b < (int64_t)P->level.size(); ++b)
-    for (int64_t k = P->loff[1][b]; k < P->loff[1][b + 1]; ++k) {
-      const int64_t a = P->lidx[1][k];
-      int o[3];
-      for (int d = 0; d < 3; ++d) {
-        o[d] = (int)(P->anchor[3 * a + d] - P->anchor[3 * b + d]);
-        if (sym) o[d] = std::abs(o[d]);
-      }
-      m2l_used[P->level[b]][m2l_code(o[0], o[1], o[2])] = 1;
+  for (int l = 0; l <= maxl; ++l)
+    for (int c = 0; c < 343; ++c) {
+      const int x = c / 49 - 3, y = (c / 7) % 7 - 3, z = c % 7 - 3;
+      if (used[l][c]) m2l_used[l][sym ? m2l_code(std::abs(x), std::abs(y), std::abs(z)) : c] = 1;
     }
   std::vector<char> has_children(maxl + 1, 0);
   for (int64_t b = 0; b < (int64_t)P->level.size(); ++b)
@@ -862,63 +884,74 @@ static int upload_lists(fmm_plan *P) {
   // children present), so that the columns of one 16-wide MFMA block mostly
   // hold the same children.
   {
-    struct Col { int32_t tgt; int32_t src[8]; int32_t key; uint8_t flip; };
-    std::vector<Col> cols;
+    struct Col { int32_t src[8]; int32_t key; uint8_t flip; };
     const int64_t b2 = P->level_begin.size() > 2 ? P->level_begin[2] : nb;
     if (P->loff[1][b2] != 0) {
       set_error("internal: V lists above level 2");
       return FMM_EINVAL;
     }
-    std::vector<int32_t> vt, vo;
-    std::vector<int64_t> cursor((size_t)(MAXLEVEL + 1) * 27 * 256 + 1, 0);
-    for (int64_t b = b2; b < nb; ++b) {
-      vt.push_back((int32_t)b);
-      vo.push_back((int32_t)cols.size());
-      for (int64_t k = P->loff[1][b]; k < P->loff[1][b + 1];) {
-        const int64_t pa = P->parent[P->lidx[1][k]], pb = P->parent[b];
-        Col c;
-        c.tgt = (int32_t)b;
-        c.flip = 0;
-        std::fill(c.src, c.src + 8, -1);
-        int shape = 0;
-        for (int d = 0; d < 3; ++d) {
-          int64_t off = P->anchor[3 * pa + d] - P->anchor[3 * pb + d];
-          int t = (int)(P->anchor[3 * b + d] & 1);
-          if (off < 0 || (off == 0 && t == 1)) {
-            c.flip |= (uint8_t)(4 >> d);
-            off = -off;
-            t ^= 1;
-          }
-          shape = shape * 3 + (off == 0 ? 0 : 1 + t);
+    // every box at level >= 2 gets its sum (possibly empty)
+    std::vector<int32_t> vt((size_t)(nb - b2)), vo((size_t)(nb - b2) + 1, 0);
+    parallel_ranges(nb - b2, 4096, [&](int64_t i0, int64_t i1) {
+      for (int64_t i = i0; i < i1; ++i) {
+        vt[i] = (int32_t)(b2 + i);
+        int64_t last = -1;
+        for (int64_t k = P->loff[1][b2 + i]; k < P->loff[1][b2 + i + 1]; ++k) {
+          const int64_t pa = P->parent[P->lidx[1][k]];
+          vo[i + 1] += pa != last;
+          last = pa;
         }
-        int mask = 0;
-        for (; k < P->loff[1][b + 1] && P->parent[P->lidx[1][k]] == pa; ++k) {
-          const int64_t a = P->lidx[1][k];
-          int oct = (int)(((P->anchor[3 * a] & 1) << 2) | ((P->anchor[3 * a + 1] & 1) << 1) | (P->anchor[3 * a + 2] & 1));
-          oct ^= c.flip;
-          c.src[oct] = (int32_t)a;
-          mask |= 1 << oct;
-        }
-        c.key = (P->level[b] * 27 + shape) * 256 + (mask ^ (mask >> 1));
-        cursor[c.key + 1]++;
-        cols.push_back(c);
       }
-    }
-    vo.push_back((int32_t)cols.size());
+    });
+    for (size_t i = 1; i < vo.size(); ++i) vo[i] += vo[i - 1];
+    const int64_t nc = vo.back();
+    std::unique_ptr<Col[]> cols(new Col[(size_t)nc]);
+    parallel_ranges(nb - b2, 4096, [&](int64_t i0, int64_t i1) {
+      Col *out = cols.get() + vo[i0];
+      for (int64_t b = b2 + i0; b < b2 + i1; ++b)
+        for (int64_t k = P->loff[1][b]; k < P->loff[1][b + 1];) {
+          const int64_t pa = P->parent[P->lidx[1][k]], pb = P->parent[b];
+          Col &c = *out++;
+          c.flip = 0;
+          std::fill(c.src, c.src + 8, -1);
+          int shape = 0;
+          for (int d = 0; d < 3; ++d) {
+            int64_t off = P->anchor[3 * pa + d] - P->anchor[3 * pb + d];
+            int t = (int)(P->anchor[3 * b + d] & 1);
+            if (off < 0 || (off == 0 && t == 1)) {
+              c.flip |= (uint8_t)(4 >> d);
+              off = -off;
+              t ^= 1;
+            }
+            shape = shape * 3 + (off == 0 ? 0 : 1 + t);
+          }
+          int mask = 0;
+          for (; k < P->loff[1][b + 1] && P->parent[P->lidx[1][k]] == pa; ++k) {
+            const int64_t a = P->lidx[1][k];
+            int oct = (int)(((P->anchor[3 * a] & 1) << 2) | ((P->anchor[3 * a + 1] & 1) << 1) | (P->anchor[3 * a + 2] & 1));
+            oct ^= c.flip;
+            c.src[oct] = (int32_t)a;
+            mask |= 1 << oct;
+          }
+          c.key = (P->level[b] * 27 + shape) * 256 + (mask ^ (mask >> 1));
+        }
+    });
+    std::vector<int32_t> cursor((size_t)(D.maxlevel + 1) * 27 * 256 + 1, 0);
+    for (int64_t i = 0; i < nc; ++i) cursor[cols[i].key + 1]++;
     for (size_t i = 1; i < cursor.size(); ++i) cursor[i] += cursor[i - 1];
-    const int64_t nc = (int64_t)cols.size();
+    std::vector<int32_t> vpp((size_t)nc);
+    for (int64_t i = 0; i < nc; ++i) vpp[i] = cursor[cols[i].key]++;
     P->mcol_src.resize((size_t)nc * 8);
     P->mcol_key.resize((size_t)nc);
     P->mcol_flip.resize((size_t)nc);
-    std::vector<int32_t> vpp((size_t)nc);
-    for (int64_t i = 0; i < nc; ++i) {
-      const int64_t pos = cursor[cols[i].key]++;
-      std::copy(cols[i].src, cols[i].src + 8, &P->mcol_src[(size_t)pos * 8]);
-      P->mcol_key[pos] = cols[i].key / 256;
-      P->mcol_flip[pos] = cols[i].flip;
-      vpp[i] = (int32_t)pos;
-    }
-    // every box at level >= 2 gets its sum (possibly empty)
+    parallel_ranges(nc, 16384, [&](int64_t i0, int64_t i1) {
+      for (int64_t i = i0; i < i1; ++i) {
+        const int64_t pos = vpp[i];
+        std::copy(cols[i].src, cols[i].src + 8, &P->mcol_src[(size_t)pos * 8]);
+        P->mcol_key[pos] = cols[i].key / 256;
+        P->mcol_flip[pos] = cols[i].flip;
+      }
+    });
     D.nvbox = (int)vt.size();
     D.nvcol = nc;
     if ((rc = upload(P, (void **)&D.v_tgt, vt))) return rc;
@@ -1024,14 +1057,12 @@ static int m2l_columns(fmm_plan *P, int nr) {
   for (int l = 2; l <= maxl; ++l) M.nrbk = std::max(M.nrbk, r16(O.rank_u[l]) / 16);
   M.ldy = pair_ld(P, 0);
   std::vector<M2LTask> tasks;
-  std::vector<int32_t> msrc;
   struct Group { int64_t cost; int level, first, count; };
   std::vector<Group> groups;
   for (int64_t i = 0, j; i < nc; i = j) {
     const int l = P->mcol_key[i] / 27, shape = P->mcol_key[i] % 27;
     for (j = i; j < nc && P->mcol_key[j] == P->mcol_key[i]; ++j) {}
     groups.push_back({0, l, (int)tasks.size(), 0});
-    const int sh[3] = {shape / 9, (shape / 3) % 3, shape % 3};
     for (int64_t c0 = i * nr; c0 < j * nr; c0 += M.nt) {
       M2LTask t;
       std::memset(&t, 0, sizeof(t));
@@ -1040,33 +1071,69 @@ static int m2l_columns(fmm_plan *P, int nr) {
       t.nrb = r16(O.rank_d[l]) / 16;
       t.klen = kround(P, O.rank_u[l]);
       t.tab = l;
-      if (c0 > 0x7fffffff - M.nt || msrc.size() > 0x7fffffffu - 8 * (size_t)M.nt) {
-        set_error("too many V pairs");
-        return FMM_EINVAL;
-      }
-      t.src0 = (int32_t)msrc.size();
-      for (int oct = 0; oct < 8; ++oct) {
-        uint32_t blocks = 0;
-        for (int c = 0; c < t.ncol; ++c)
-          if (P->mcol_src[(size_t)((c0 + c) / nr) * 8 + oct] >= 0) blocks |= 1u << (c / 16);
-        if (!blocks) continue;
-        int o[3];
-        for (int d = 0; d < 3; ++d) o[d] = (sh[d] ? 2 : 0) + ((oct >> (2 - d)) & 1) - (sh[d] == 2 ? 1 : 0);
-        t.mat[t.nseg] = O.m2l_id[l][m2l_code(o[0], o[1], o[2])];
-        if (t.mat[t.nseg] < 0) { set_error("internal: M2L task references a missing operator"); return FMM_EINVAL; }
-        t.blocks |= (uint64_t)blocks << (8 * t.nseg);
-        t.zero[t.nseg] = (uint8_t)((o[0] ? 0 : 4) | (o[1] ? 0 : 2) | (o[2] ? 0 : 1));
-        ++t.nseg;
-        for (int c = 0; c < M.nt; ++c) {
-          const int32_t a = c < t.ncol ? P->mcol_src[(size_t)((c0 + c) / nr) * 8 + oct] : -1;
-          msrc.push_back(a < 0 ? -1 : a * nr + (int32_t)((c0 + c) % nr));
-        }
-      }
-      groups.back().cost += (int64_t)t.nseg * t.nrb * t.klen;
+      t.pad = shape;
+      if (c0 > 0x7fffffff - M.nt) { set_error("too many V pairs"); return FMM_EINVAL; }
       ++groups.back().count;
       tasks.push_back(t);
     }
   }
+  // the segments of each task, then their source rows
+  const int64_t nt = (int64_t)tasks.size();
+  std::vector<uint8_t> octs((size_t)nt);  // octants of the children that some column holds
+  std::atomic<bool> missing(false);
+  parallel_ranges(nt, 256, [&](int64_t i0, int64_t i1) {
+    for (int64_t i = i0; i < i1; ++i) {
+      M2LTask &t = tasks[i];
+      const int shape = t.pad, sh[3] = {shape / 9, (shape / 3) % 3, shape % 3};
+      t.pad = 0;
+      uint32_t blocks[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+      int64_t col = t.col0 / nr;
+      for (int c = 0, r = t.col0 % nr; c < t.ncol; ++c) {
+        const int32_t *src = &P->mcol_src[(size_t)col * 8];
+        for (int oct = 0; oct < 8; ++oct) blocks[oct] |= (uint32_t)(src[oct] >= 0) << (c / 16);
+        if (++r == nr) { r = 0; ++col; }
+      }
+      for (int oct = 0; oct < 8; ++oct) {
+        if (!blocks[oct]) continue;
+        octs[i] |= (uint8_t)(1 << oct);
+        int o[3];
+        for (int d = 0; d < 3; ++d) o[d] = (sh[d] ? 2 : 0) + ((oct >> (2 - d)) & 1) - (sh[d] == 2 ? 1 : 0);
+        t.mat[t.nseg] = O.m2l_id[t.tab][m2l_code(o[0], o[1], o[2])];
+        if (t.mat[t.nseg] < 0) missing = true;
+        t.blocks |= (uint64_t)blocks[oct] << (8 * t.nseg);
+        t.zero[t.nseg] = (uint8_t)((o[0] ? 0 : 4) | (o[1] ? 0 : 2) | (o[2] ? 0 : 1));
+        ++t.nseg;
+      }
+    }
+  });
+  if (missing) { set_error("internal: M2L task references a missing operator"); return FMM_EINVAL; }
+  int64_t nsrc = 0;
+  for (M2LTask &t : tasks) {
+    t.src0 = (int32_t)nsrc;
+    nsrc += (int64_t)t.nseg * M.nt;
+    if (nsrc > 0x7fffffff) { set_error("too many V pairs"); return FMM_EINVAL; }
+  }
+  std::unique_ptr<int32_t[]> msrc(new int32_t[(size_t)nsrc]);
+  parallel_ranges(nt, 256, [&](int64_t i0, int64_t i1) {
+    for (int64_t i = i0; i < i1; ++i) {
+      const M2LTask &t = tasks[i];
+      int32_t *out = msrc.get() + t.src0;
+      for (int oct = 0; oct < 8; ++oct) {
+        if (!((octs[i] >> oct) & 1)) continue;
+        int64_t col = t.col0 / nr;
+        for (int c = 0, r = t.col0 % nr; c < t.ncol; ++c) {
+          const int32_t a = P->mcol_src[(size_t)col * 8 + oct];
+          out[c] = a < 0 ? -1 : a * nr + r;
+          if (++r == nr) { r = 0; ++col; }
+        }
+        std::fill(out + t.ncol, out + M.nt, -1);
+        out += M.nt;
+      }
+    }
+  });
+  for (Group &gr : groups)
+    for (int i = gr.first; i < gr.first + gr.count; ++i)
+      gr.cost += (int64_t)tasks[i].nseg * tasks[i].nrb * tasks[i].klen;
   // launch order: the shapes whose tasks are longest first (a short last round
   // of workgroups), the levels of the two M2L launches of m2l_early apart
   const int ls = std::max(2, maxl - 1);
@@ -1082,9 +1149,9 @@ static int m2l_columns(fmm_plan *P, int nr) {
   }
   M.ntask = (int)ordered.size();
   if ((rc = upload(P, (void **)&M.d_tasks, ordered))) return rc;
-  if ((rc = upload(P, (void **)&M.d_src, msrc))) return rc;
+  if ((rc = plan_upload(P, (void **)&M.d_src, msrc.get(), (size_t)nsrc * sizeof(int32_t)))) return rc;
   std::vector<uint8_t> mflip((size_t)(nc * nr));
-  for (int64_t c = 0; c < nc * nr; ++c) mflip[c] = P->mcol_flip[c / nr];
+  for (int64_t c = 0; c < nc; ++c) std::fill_n(&mflip[(size_t)c * nr], nr, P->mcol_flip[c]);
   if ((rc = upload(P, (void **)&M.d_flip, mflip))) return rc;
   return FMM_OK;
 }
@@ -1247,10 +1314,10 @@ int ensure_lists(fmm_plan *P, int nr, int set) {
       bt.set = set;
       bt.nrb = r16(O.rank_u[l]) / 16;
       bt.klen = r16(O.rank_u[l + 1]);
+      std::vector<int64_t> kids_of[8];
+      for (int64_t b = P->level_begin[l + 1]; b < P->level_begin[l + 2]; ++b) kids_of[oct_of(b)].push_back(b);
       for (int oct = 0; oct < 8; ++oct) {
-        std::vector<int64_t> kids;
-        for (int64_t b = P->level_begin[l + 1]; b < P->level_begin[l + 2]; ++b)
-          if (oct_of(b) == oct) kids.push_back(b);
+        const std::vector<int64_t> &kids = kids_of[oct];
         if (kids.empty()) continue;
         cols_for(kids, kids);
         add_columns(bt, O.m2m_id[l][oct], 1.0, src, dst);
@@ -1273,13 +1340,13 @@ int ensure_lists(fmm_plan *P, int nr, int set) {
       bt.mode = GEMM_ADD;
       bt.nrb = r16(O.rank_d[l]) / 16;
       bt.klen = r16(O.rank_d[l - 1]);
+      std::vector<int64_t> parents[8], boxes[8];
+      for (int64_t b : all) {
+        parents[oct_of(b)].push_back(P->parent[b]);
+        boxes[oct_of(b)].push_back(b);
+      }
       for (int oct = 0; oct < 8; ++oct) {
-        std::vector<int64_t> bs, bd;
-        for (int64_t b : all) {
-          if (oct_of(b) != oct) continue;
-          bs.push_back(P->parent[b]);
-          bd.push_back(b);
-        }
+        const std::vector<int64_t> &bs = parents[oct], &bd = boxes[oct];
         if (bd.empty()) continue;
         cols_for(bs, bd);
         add_columns(bt, O.l2l_id[l - 1][oct], 1.0, src, dst);
@@ -1783,11 +1850,13 @@ static int setup_common(const double *xyz_dev, const std::vector<int64_t> &off, 
     // the sets that the plan's evaluations take: those of live plans, the
     // others built
     take_ops(P, sets);
+    std::vector<std::vector<char>> used;
     for (int set = 0; set < 2 && !rc; ++set) {
       if (!((sets >> set) & 1) || P->ops[set].built) continue;
       P->ops[set].mem = std::make_shared<SharedAllocs>();
       P->alloc_sink = &P->ops[set].mem->ptrs;
-      rc = precision == FMM_FP64 ? precompute_typed<double>(P, set) : precompute_typed<float>(P, set);
+      if (used.empty()) used = used_offsets(P);
+      rc = precision == FMM_FP64 ? precompute_typed<double>(P, set, used) : precompute_typed<float>(P, set, used);
     }
     if (!rc && !P->geom_mem) {
       P->geom_mem = std::make_shared<SharedAllocs>();
