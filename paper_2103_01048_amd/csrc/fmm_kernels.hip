@@ -2691,10 +2691,10 @@ static int build_chain(fmm_plan *A, fmm_plan *B, bool keeps, bool up, Chain &C) 
   return FMM_OK;
 }
 
-// Both chains current for (A, B, NR) and a counter array for them (ticket
-// and phase counters of each chain, then the error flag).
+// Both chains of one kind of evaluation current for (A, B, NR) and a counter
+// array for them (ticket and phase counters of each chain, then the error flag).
 template <typename T, int NR>
-static int ensure_chains(fmm_plan *A, fmm_plan *B, bool keeps) {
+static int ensure_chains_of(fmm_plan *A, fmm_plan *B, bool keeps) {
   Chain &up = A->chain_up[keeps], &down = A->chain_down[keeps];
   const std::vector<const void *> key = {B, (const void *)(intptr_t)NR, A->cu, A->mslot, A->yd, B->cu, B->mslot, B->yd};
   int rc;
@@ -2710,6 +2710,16 @@ static int ensure_chains(fmm_plan *A, fmm_plan *B, bool keeps) {
     A->chain_ctr_n = n;
   }
   return FMM_OK;
+}
+
+// One column: the chains of the other kind of evaluation too, which could not be
+// built inside a graph capture.
+template <typename T, int NR>
+static int ensure_chains(fmm_plan *A, fmm_plan *B, bool keeps) {
+  if constexpr (NR == 1) {
+    if (int rc = ensure_chains_of<T, NR>(A, B, !keeps)) return rc;
+  }
+  return ensure_chains_of<T, NR>(A, B, keeps);
 }
 
 template <typename T>

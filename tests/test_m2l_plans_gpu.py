@@ -65,6 +65,15 @@ def _operator(precision, level=4):
     return BEMOperator(v, t, quad_pts=3, kappa=KAPPA, p=6, ncrit=32, precision=precision)
 
 
+def _operator_points(torch, level=4):
+    """The quadrature points of _operator, to the bit."""
+    v, t = synth.octa_sphere(level, 4.0)
+    l1, l2 = np.array([1 / 6, 2 / 3, 1 / 6])[None, :, None], np.array([1 / 6, 1 / 6, 2 / 3])[None, :, None]
+    tri = v[t][:, None]
+    x = ((1 - l1 - l2) * tri[:, :, 0] + l1 * tri[:, :, 1] + l2 * tri[:, :, 2]).reshape(-1, 3)
+    return torch.tensor(x, device="cuda")
+
+
 class _OperatorPlans:
     """The operator's two plans (bem_fmm_plan) as FMMPlans that do not own
     their handles."""
@@ -72,7 +81,7 @@ class _OperatorPlans:
     def __init__(self, torch, op):
         import ctypes
         from paper_2103_01048_amd import FMMPlan, _lib
-        self.plans = []
+        self.op, self.plans = op, []
         for name, kernel in (("laplace", _lib.FMM_LAPLACE), ("yukawa", _lib.FMM_YUKAWA)):
             pl = FMMPlan.__new__(FMMPlan)
             pl._h = ctypes.c_void_p(_lib.lib().bem_fmm_plan(op._h, kernel))
@@ -87,6 +96,7 @@ class _OperatorPlans:
     def __exit__(self, *a):
         for pl in self.plans:
             pl._h = None
+        self.op = None
 
 
 @pytest.mark.parametrize("precision", ["bf16x3", "fp32", "fp64"])
@@ -170,24 +180,26 @@ def _replay_equals_eager(torch, warm, fn):
 
 
 @pytest.mark.parametrize("precision", ["bf16x3", "fp32", "fp64"])
-@pytest.mark.parametrize("form", ["single after pair", "pair after products", "single after five columns"])
+@pytest.mark.parametrize("form", ["single after pair", "pair after products", "single after five columns",
+                                  "chained pair after products"])
 def test_one_column_captured_after_another_form_of_evaluation(precision, form):
     """A plan that has evaluated one column in one way evaluates one in
     another inside a graph capture, where nothing can be allocated."""
     torch = require_gpu()
-    from paper_2103_01048_amd import eval_pair
+    from paper_2103_01048_amd import autotune, eval_pair
     from paper_2103_01048_amd.fmm import eval_pair_md
     xt = torch.tensor(_cloud(), device="cuda")
     dt = torch.float64 if precision == "fp64" else torch.float32
     rng = np.random.default_rng(165)
     q = torch.tensor(rng.standard_normal((5, len(xt))), device="cuda", dtype=dt)
     dip = torch.tensor(rng.standard_normal((len(xt), 3)), device="cuda", dtype=dt)
-    a, b = _plans(xt, precision)
+    with autotune.tuning(**{**autotune.DEFAULTS, "gemm_chain": int(form.startswith("chained"))}):
+        a, b = _plans(xt, precision)
     assert _m2l_columns(a) >= 1024
     print(f"[m2l plans] capture {precision} {form}", flush=True)
     if form == "single after pair":
         _replay_equals_eager(torch, lambda: eval_pair(a, b, q[0]), lambda: list(b.eval(q[1])))
-    elif form == "pair after products":
+    elif form.endswith("pair after products"):
         _replay_equals_eager(torch, lambda: eval_pair_md(a, b, q[0], dip),
                              lambda: [t for o in eval_pair(a, b, q[1]) for t in o])
     else:
@@ -215,10 +227,7 @@ def test_plan_takes_the_operators_that_a_live_operator_has(precision):
     that the operator does not hold, keeps what it took when the operator is
     freed, and gives the same results to the bit as one that built them all."""
     torch = require_gpu()
-    v, t = synth.octa_sphere(4, 4.0)
-    l1, l2 = np.array([1 / 6, 2 / 3, 1 / 6])[None, :, None], np.array([1 / 6, 1 / 6, 2 / 3])[None, :, None]
-    tri = v[t][:, None]
-    x = torch.tensor(((1 - l1 - l2) * tri[:, :, 0] + l1 * tri[:, :, 1] + l2 * tri[:, :, 2]).reshape(-1, 3), device="cuda")
+    x = _operator_points(torch)
     dt = torch.float64 if precision == "fp64" else torch.float32
     q = torch.tensor(np.random.default_rng(167).standard_normal((2, len(x))), device="cuda", dtype=dt)
 
@@ -244,3 +253,22 @@ def test_plan_takes_the_operators_that_a_live_operator_has(precision):
     for a, b in zip(results(plans), want):
         assert torch.equal(a, b)
     del junk
+
+
+@pytest.mark.parametrize("cols", [1, 3])
+@pytest.mark.parametrize("precision,tol", [("bf16x3", 1e-5), ("fp32", 1e-6)])
+def test_pair_of_an_operators_plan_and_a_plan_of_the_callers(precision, tol, cols):
+    """One plan in the pairwise and one in the segmented form: two M2L launches
+    and two sums, the other passes of both in one launch.  The two forms differ
+    by rounding (sums of about 200 terms in FP32; bf16x3 products rounded to
+    2^-16 of the far field)."""
+    torch = require_gpu()
+    x = _operator_points(torch)
+    q = torch.tensor(np.random.default_rng(168).standard_normal((cols, len(x))), device="cuda", dtype=torch.float32)
+    print(f"[m2l plans] mixed forms {precision} {cols}", flush=True)
+    plans = _plans(x, precision)
+    want = _pair(plans, q)
+    with _OperatorPlans(torch, _operator(precision)) as of_op:
+        for mixed in ([of_op[0], plans[1]], [plans[0], of_op[1]], of_op):
+            for got, ref in zip(_pair(mixed, q), want):
+                assert float((got.double() - ref.double()).norm() / ref.double().norm()) < tol
