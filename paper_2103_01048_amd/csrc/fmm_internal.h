@@ -48,15 +48,17 @@ int tsvd_split(int rows, int cols, const double *A, double tau, double *L, int l
 // Which operator set an evaluation of plan P takes.  Set 0 (segmented M2L) is
 // the faster one but adds a target's sources in another order than set 1
 // (pairwise M2L).  Set 1 serves the factored operators and, in single
-// precision, the two kinds of evaluation whose results are handed on in
-// double precision (`keeps_order`): one column of one plan (the gradients of
-// autograd.py) and monopole + dipole sources (the boundary-element products).
-// Those keep their order of summation and with it every bit.  The plans of a
-// boundary-element operator take set 1 for every evaluation: one that a caller
-// takes out by bem_fmm_plan finds the operators that its setup built, and no
-// evaluation builds operators.  Single precision takes set 1 for a few columns too (fewer than M2L_FEW_COLUMNS):
-// its launch spreads V pairs over the chip where the segmented one walks up to
-// eight segments in a few workgroups (600 points: 18.5 against 26.6 us).
+// precision, two kinds of evaluation that keep their order of summation and
+// with it every bit (`keeps_order`): one column of one plan, whose gradients
+// autograd.py hands on in the caller's double precision (the last column of
+// nrhs = 5, 9, ... is evaluated as one column, and so to the same bits as on its
+// own), and monopole + dipole sources (the boundary-element products).  The
+// plans of a boundary-element operator take set 1 for every evaluation: one
+// that a caller takes out by bem_fmm_plan finds the operators that its setup
+// built, and no evaluation builds operators.  Plans of few M2L columns (fewer than
+// M2L_FEW_COLUMNS, whatever the number of densities) take set 1 too: its launch
+// spreads V pairs over the chip where the segmented one walks up to eight
+// segments in a few workgroups (600 points: 18.5 against 26.6 us).
 inline int op_set(const fmm_plan *P, bool keeps_order);
 
 #define FMM_HIP_TRY(call)                                                        \

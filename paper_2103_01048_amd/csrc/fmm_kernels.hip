@@ -41,9 +41,10 @@ __device__ inline doublex4 mfma_16x16x4(double a, double b, doublex4 c) {
 }
 
 __device__ inline float dev_rsqrt(float x) { return __builtin_amdgcn_rsqf(x); }
-// FP64 reciprocal square root, x > 0: the hardware estimate y refined by one
-// step of third order, y (1 + e/2 + 3/8 e^2) with e = 1 - x y^2: the estimate's
-// ~2^-22 becomes 2^-65 before rounding, and the correction is added by one fused
+// FP64 reciprocal square root, x > 0: the hardware estimate y refined by the
+// binomial series of (1 - e)^(-1/2), e = 1 - x y^2, to its second term (one step
+// of third order): y (1 + e/2 + 3/8 e^2), which takes the estimate's
+// ~2^-22 to 2^-65 before rounding; the correction is added by one fused
 // multiply-add.  Largest error over 2^20 values of 1e-12..1e12 against 64 bits
 // of mantissa: 1.4e-16 (two Newton-Raphson steps with their tests: 2.6e-16).
 // Callers that may meet x = 0 select its value.
@@ -1185,8 +1186,9 @@ __device__ inline void pair_gf(T r2, T kappa, T &g, T &f) {
 // each range.  Sub-waves therefore test for a missing source only in a range's
 // last step: the whole steps' loads take a uniform base and no selects (six of
 // about 31 instructions a step).  The next range's bounds and shift are loaded
-// while a range is summed.  Unrolled by 4 (FP64 2: registers).  Same sums in
-// the same order as with a test in each step; passes with that / with this:
+// while a range is summed.  The whole steps of a range without the tile's own
+// leaf are unrolled by 4 (by 2 for FP64 in the pair kernels: registers), of the
+// range with it by 2.  Same sums in the same order as with a test in each step; passes with that / with this:
 // 9000-point pair evaluation 301 / 275 us, 393216-point pair evaluation 1083 /
 // 1045 us, 100003-point Yukawa sum of 4 columns 805 / 726 us, potential and
 // adjoint of 1000002 points 4270 / 4092 us.  Not taken: a tile's remainder of
@@ -2372,11 +2374,6 @@ static int launch_m2l(fmm_plan *P, fmm_plan *Q, int nr, int l0, int l1, hipStrea
   const int nrb = std::max(g0.nrb, g1.ntask ? g1.nrb : 0);
   const int nt = P->lists[0][nr].m2lc.nt;
   const unsigned gx = (unsigned)(m2l_grid(g0.ntask) + m2l_grid(g1.ntask));
-  // Waves of a workgroup, two row blocks each (few registers, so that a SIMD
-  // holds four and more waves to hide the operator loads): as many as the rank
-  // needs up to 6 in single precision; 3 in double, whose larger ranks, like
-  // single precision's from 13 row blocks and a lower gemm_rbw, split the
-  // rows over the grid.
   if (P->precision == FMM_FP32_BF16X3) {
     // the boxes of the levels [l0, l1); a row past the last box stays zero
     // (both plans share the tree, so their rows and their task counts agree)
