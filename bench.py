@@ -67,10 +67,26 @@ FLOP_PER_PAIR_STD = 45
 FLOP_PER_SURF_PAIR = 17
 
 
-def phase_work(plan_l, plan_y, infos):
+# the single-precision pair evaluation takes the segmented M2L from this many
+# columns on (M2L_FEW_COLUMNS of csrc/fmm_internal.h)
+M2L_FEW_COLUMNS = 1024
+
+
+def m2l_slots(tree, factored):
+    """Product slots that the M2L sums of a pair evaluation read per plan: one
+    per target box and source parent (segmented M2L), or one per V pair."""
+    parent = tree["parent"]
+    cols = sum(len({int(parent[a]) for a in v}) for v in tree["V"])
+    if factored or cols < M2L_FEW_COLUMNS:
+        return sum(len(v) for v in tree["V"])
+    return cols
+
+
+def phase_work(plan_l, plan_y, infos, factored=False):
     """Algorithmic work of each phase of one pair step (both kernels, one
     column) and the peak that bounds it.  Translation counts use each plan's
-    largest rank (an upper bound where the ranks vary by level)."""
+    largest rank (an upper bound where the ranks vary by level).  factored:
+    the plans' m2l_factored."""
     tl = plan_l.tree()
     lev = tl["level"]
     nch = tl["nchild"]
@@ -91,12 +107,13 @@ def phase_work(plan_l, plan_y, infos):
     ranks = [(inf_l["rank_up"], inf_l["rank_down"]), (inf_y["rank_up"], inf_y["rank_down"])]
     gemm = lambda f: float(sum(f(ru, rd) for ru, rd in ranks))
     nv = inf_l["n_v_pairs"]
+    nslot = m2l_slots(tl, factored)
     work = {
         "p2m": (p2m_pairs * FLOP_PER_SURF_PAIR, PEAK_VALU_FP32, "flop"),
         "uc2e": (gemm(lambda ru, rd: 2.0 * ru * ns * nleaf2), PEAK_MFMA["fp32"], "flop"),
         "m2m": (gemm(lambda ru, rd: 2.0 * ru * ru * child2), PEAK_MFMA["fp32"], "flop"),
         "m2l": (gemm(lambda ru, rd: 2.0 * ru * rd * nv), PEAK_BF16X3_USEFUL, "flop"),
-        "m2l_sum": (gemm(lambda ru, rd: 4.0 * rd * nv), PEAK_HBM, "byte"),
+        "m2l_sum": (gemm(lambda ru, rd: 4.0 * rd * nslot), PEAK_HBM, "byte"),
         "p2l": (p2l_pairs * FLOP_PER_SURF_PAIR, PEAK_VALU_FP32, "flop"),
         "dc2e": (gemm(lambda ru, rd: 2.0 * rd * ns * (p2l_boxes + nleaf2)), PEAK_MFMA["fp32"], "flop"),
         "l2l": (gemm(lambda ru, rd: 2.0 * rd * rd * child2), PEAK_MFMA["fp32"], "flop"),
@@ -875,7 +892,8 @@ def main():
     # every phase: its algorithmic work, its own time (serial mode, HIP
     # events around its launches) and the fraction of its bounding peak; the
     # whole call: sum over phases of work / peak, over the timed step
-    work = phase_work(plans["laplace"], plans["yukawa"], infos)
+    work = phase_work(plans["laplace"], plans["yukawa"], infos,
+                      bool(tuned and tuned["tuning"].get("m2l_factored")))
     phases_out = {}
     ideal = 0.0
     for name, (w, peak, unit) in work.items():

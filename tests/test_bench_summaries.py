@@ -87,3 +87,14 @@ def test_kernel_digest_ignores_comments_and_whitespace_only(tmp_path):
     open(c, "w").write("__global__ void k(float *x) {\n  x[0] = 2.f;\n}\n")
     assert bench.kernel_source_digest(a) == bench.kernel_source_digest(b)
     assert bench.kernel_source_digest(a) != bench.kernel_source_digest(c)
+
+
+def test_m2l_slots_count_source_parents_of_the_segmented_form():
+    """Slots that the M2L sums read: one per target and source parent from
+    M2L_FEW_COLUMNS columns on, one per V pair below or with factored operators."""
+    import bench
+    n = bench.M2L_FEW_COLUMNS
+    tree = {"parent": [0, 0, 0, 1, 1], "V": [[0, 1, 2, 3]] * (n // 2) + [[]]}
+    assert bench.m2l_slots(tree, False) == n
+    assert bench.m2l_slots(tree, True) == 4 * (n // 2)
+    assert bench.m2l_slots(dict(tree, V=tree["V"][1:]), False) == 4 * (n // 2 - 1)
