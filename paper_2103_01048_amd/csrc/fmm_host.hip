@@ -1049,7 +1049,7 @@ static int m2l_columns(fmm_plan *P, int nr) {
     for (j = i; j < nc && P->mcol_key[j] == P->mcol_key[i]; ++j) {}
     wide += ((j - i) * nr + GEMM_NT - 1) / GEMM_NT;
   }
-  // (measured, 16 against wide columns: 600 points FP32 26.6 against 28.9 us, 8k
+  // (the M2L alone, 16 against wide columns: 600 points FP32 26.6 against 28.9 us, 8k
   // and 6k points FP64 45.5 / 52.8 against 56.1 / 72.9 us; 42k points bf16x3,
   // 192 wide tasks per plan, 70.8 against 44.0 us)
   M.nt = wide < M2L_WIDE_TASKS ? 16 : P->precision == FMM_FP64 ? 32 : P->precision == FMM_FP32 ? GEMM_NT : P->tune.m2l_cols;

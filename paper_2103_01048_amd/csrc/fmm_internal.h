@@ -58,7 +58,10 @@ int tsvd_split(int rows, int cols, const double *A, double tau, double *L, int l
 // built, and no evaluation builds operators.  Plans of few M2L columns (fewer than
 // M2L_FEW_COLUMNS, whatever the number of densities) take set 1 too: its launch
 // spreads V pairs over the chip where the segmented one walks up to eight
-// segments in a few workgroups (600 points: 18.5 against 26.6 us).
+// segments in a few workgroups.  Pair passes at p = 8, pairwise / segmented: bf16x3
+// 120 / 135 us at 85 columns, 183 / 190 at 284, within 2% of each other from 960 to
+// 2000 (p = 5 and 6: within 3.5% from 960 to 2400), 217 / 210 at 2272; FP32 133 /
+// 149 us at 85, 208 / 205 at 284, 244 / 233 at 1589.
 inline int op_set(const fmm_plan *P, bool keeps_order);
 
 #define FMM_HIP_TRY(call)                                                        \
