@@ -1614,20 +1614,16 @@ static fmm_tuning_t g_tune{32, 16, 512, 16384, 1.15, 0, 0, 4, 0, 512, 0, 64, 0, 
 static std::mutex g_tree_mu;
 static std::vector<fmm_plan *> g_tree_plans;
 
-// A live plan whose tree P can take: the same input coordinates (checksum
-// over their bits, point count and molecule ranges), root cube, ncrit,
-// surface size (the leaf items depend on it), working type and device.
-static fmm_plan *find_tree(const fmm_plan *P) {
-  std::lock_guard<std::mutex> lock(g_tree_mu);
-  for (fmm_plan *A : g_tree_plans)
-    if (A->coord_hash == P->coord_hash && A->n == P->n && A->mol_off == P->mol_off && A->W == P->W &&
-        A->mol_lo == P->mol_lo && A->ncrit == P->ncrit && A->nsurf == P->nsurf &&
-        (A->precision == FMM_FP64) == (P->precision == FMM_FP64) && A->device == P->device && A->tree_mem &&
-        A->tune.tile_split2 == P->tune.tile_split2 && A->tune.tile_split4 == P->tune.tile_split4 &&
-        A->tune.work_cap_min == P->tune.work_cap_min && A->tune.work_cap_div == P->tune.work_cap_div &&
-        A->tune.far_weight == P->tune.far_weight)
-      return A;
-  return nullptr;
+// Whether P can take A's tree: the same input coordinates (checksum over
+// their bits, point count and molecule ranges), root cube, ncrit, surface
+// size (the leaf items depend on it), working type and device.
+static bool same_tree(const fmm_plan *A, const fmm_plan *P) {
+  return A->coord_hash == P->coord_hash && A->n == P->n && A->mol_off == P->mol_off && A->W == P->W &&
+         A->mol_lo == P->mol_lo && A->ncrit == P->ncrit && A->nsurf == P->nsurf &&
+         (A->precision == FMM_FP64) == (P->precision == FMM_FP64) && A->device == P->device && A->tree_mem &&
+         A->tune.tile_split2 == P->tune.tile_split2 && A->tune.tile_split4 == P->tune.tile_split4 &&
+         A->tune.work_cap_min == P->tune.work_cap_min && A->tune.work_cap_div == P->tune.work_cap_div &&
+         A->tune.far_weight == P->tune.far_weight;
 }
 
 // Whether P can take A's translation operators: the same kernel, kappa, order
@@ -1700,6 +1696,15 @@ static int share_tree(fmm_plan *P, const fmm_plan *A, hipStream_t s) {
   if ((rc = dev_alloc(P, &P->dt.pts, (size_t)P->n * 4 * es))) return rc;
   FMM_HIP_TRY(hipMemcpyAsync(P->dt.pts, A->dt.pts, (size_t)P->n * 4 * es, hipMemcpyDeviceToDevice, s));
   if ((rc = dev_alloc(P, &P->dt.parts, std::max<size_t>(1, (size_t)P->dt.nparts) * MAX_NR * 4 * 64 * es))) return rc;
+  return FMM_OK;
+}
+
+// P takes the tree of a live plan where one has it (tree_shared), under the lock,
+// in which that plan cannot be freed.
+static int take_tree(fmm_plan *P, hipStream_t s) {
+  std::lock_guard<std::mutex> lock(g_tree_mu);
+  for (const fmm_plan *A : g_tree_plans)
+    if (same_tree(A, P)) return share_tree(P, A, s);
   return FMM_OK;
 }
 
@@ -1784,10 +1789,10 @@ static int setup_common(const double *xyz_dev, const std::vector<int64_t> &off, 
     for (int m = 0; m < nmol; ++m)
       for (int d = 0; d < 3; ++d) P->mol_lo[3 * m + d] = cen[3 * m + d] - 0.5 * P->W;
     for (int d = 0; d < 3; ++d) { P->lo[d] = P->mol_lo[d]; P->shift[d] = P->lo[d] + 0.5 * P->W; }
-    if (fmm_plan *A = find_tree(P)) {
-      // a live plan on the same points, ncrit, surface size and working
-      // type: take its tree, lists and leaf items instead of building them
-      if ((rc = share_tree(P, A, s))) break;
+    // a live plan on the same points, ncrit, surface size and working type:
+    // take its tree, lists and leaf items instead of building them
+    if ((rc = take_tree(P, s))) break;
+    if (P->tree_shared) {
       lap(3);
     } else {
     P->tree_mem = std::make_shared<SharedAllocs>();

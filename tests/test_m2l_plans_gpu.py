@@ -272,3 +272,32 @@ def test_pair_of_an_operators_plan_and_a_plan_of_the_callers(precision, tol, col
         for mixed in ([of_op[0], plans[1]], [plans[0], of_op[1]], of_op):
             for got, ref in zip(_pair(mixed, q), want):
                 assert float((got.double() - ref.double()).norm() / ref.double().norm()) < tol
+
+
+def test_threads_set_up_evaluate_and_free_plans_on_the_same_points():
+    """Plans take trees and operators from plans that other threads free."""
+    import threading
+    torch = require_gpu()
+    xt = torch.tensor(_cloud(700), device="cuda")
+    q = torch.tensor(np.random.default_rng(169).standard_normal(len(xt)), device="cuda", dtype=torch.float32)
+    want = _pair(_plans(xt, "fp32", p=4), q)
+    torch.cuda.synchronize()
+    wrong, failed = [], []
+    print("[m2l plans] threads", flush=True)
+
+    def work():
+        try:
+            for _ in range(5):
+                with torch.cuda.stream(torch.cuda.Stream()):
+                    got = _pair(_plans(xt, "fp32", p=4), q)
+                    torch.cuda.current_stream().synchronize()
+                wrong.extend(i for i, (a, b) in enumerate(zip(got, want)) if not torch.equal(a, b))
+        except Exception as e:  # reported by the main thread
+            failed.append(repr(e))
+
+    threads = [threading.Thread(target=work) for _ in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed and not wrong
